@@ -195,13 +195,14 @@ mslm_status mslm_q_exact_variant(const int64_t *q_components, int32_t n_slices, 
  * mslm_batch_leiden uses the one of the graph its first solve names, the server the defaults.
  *   graphs             1: the sweeps of an aggregated level are replayed from a captured HIP graph
  *                      after the second sweep (default 0: plain launches)
- *   latency_units      aggregated levels: colour batches of at most this many units take the
- *                      one-launch latency path (64..65536, default 1024)
- *   split_group_units  level 0: a colour batch with at least this many lane-group units gives
- *                      them a launch of their own (0..2^30, default 16384)
+ *   latency_units      aggregated levels whose colour batches hold fewer units than this on
+ *                      average decide both unit classes in one kernel (64..65536, default 1024)
+ *   split_group_units  level 0: batches of at least this many units on average give their
+ *                      lane-group units a launch of their own (0..2^30, default 16384)
  *   copy_moves         level 0: the per-entry neighbour-label copy is kept through sweeps that
  *                      moved at most (units / copy_moves) units (1..2^30, default 1024)
- *   lat_parts_max      latency path: most blocks sharing one unit's candidates (1..16, default 16)
+ *   lat_parts_max      a sweep decides at least this many times 32 blocks of work ahead of the
+ *                      colour whose moves come next (1..16, default 16)
  *   batch_units        mslm_batch_leiden: most supra-nodes per union, in units of 2^20 (1..100,
  *                      default 24)
  * Errors: EINVAL for a value out of range or a NULL pointer. */

@@ -113,7 +113,7 @@ struct Workspace {
   Buf ref_wide, ref_wcnt;                 // refinement units with long rows, and their count
   Buf ref_snap_a, ref_snap_p;             // active flags and proposal stamps before a round
   Buf ref_keep;                           // active flags of solves that skip a round's redo
-  Buf lat_part, lat_done;                 // latency mode: candidates split among blocks
+  Buf win_tab, win_segs, win_items, win_state;   // colour windows of the level being swept
   // sweeps replayed from HIP graphs: a private stream (default priority) joined to the solve
   // stream by events, the fresh-label base on the device, and a switch that turns graphs off
   // after a failed capture
@@ -122,7 +122,7 @@ struct Workspace {
   bool graphs_off = false;
   Buf fresh;
   // level 0 in colour-batch order (local-moving sweeps)
-  Buf p_pos, p_deg, p_rp, p_col, p_w, p_k, p_slice, p_solve, p_iota, p_comm, p_goff, p_glg,
+  Buf p_pos, p_deg, p_rp, p_col, p_w, p_k, p_slice, p_solve, p_comm, p_goff, p_glg,
       p_wide, p_nwide, p_sk, p_sk2, p_units, p_elab, p_prev;
   LevelBufs lvA, lvB;
   std::vector<hipEvent_t> evpool;

@@ -32,14 +32,20 @@ struct SolveDev {
   const int32_t *sfirst;               // first global slice of the solve
   const int64_t *S;                    // per global slice: 2m_s, or 1 for an empty slice
   int64_t *fallbacks;                  // exact-comparison counter per solve
-  uint32_t *redo;                      // per solve: a sweep met a near-tie it could not settle
+  // per solve: the smallest mark of a near-tie that a kernel without the big-integer path could
+  // not settle (kRedoUnset: none).  Refinement marks 0; a window of colours marks the unit's
+  // colour, so that only the colours whose decisions count ask for a repeat
+  int32_t *redo;
   // during local-moving sweeps: solves that take no part in the sweep (stopped, or not being
   // taken again); their units are not decided (their moves would not be applied); else nullptr
   const uint8_t *frozen;
   // a sweep replayed from a HIP graph reads the base of its fresh labels here (its launches
   // were captured once); nullptr: the base passed to the kernel
   const uint32_t *fresh;
+  int32_t mark = 0;                    // what a near-tie writes into redo
 };
+constexpr int kRedoByte = 0x7f;
+constexpr int32_t kRedoUnset = 0x7f7f7f7f;   // four equal bytes: set by a byte fill
 
 __device__ inline uint32_t fresh_of(const SolveDev &sd, uint32_t fresh_base) {
   return sd.fresh ? *sd.fresh : fresh_base;
@@ -141,6 +147,7 @@ struct ViewP {
     return raw & 0x7fffffff;
   }
   __device__ int64_t orig(int64_t i) const { return uid[i]; }
+  __device__ int64_t unit_at(const int32_t *, int64_t pos) const { return pos; }
   __device__ uint32_t lab_at(const uint32_t *comm, int64_t e, int64_t x) const {
     return elab ? elab[e] : comm[x];
   }
@@ -172,6 +179,7 @@ struct ViewK {
     return col[e];
   }
   __device__ int64_t orig(int64_t v) const { return v; }
+  __device__ int64_t unit_at(const int32_t *units, int64_t pos) const { return units[pos]; }
   __device__ uint32_t lab_at(const uint32_t *comm, int64_t, int64_t x) const { return comm[x]; }
   __device__ int solve_of(int64_t v) const { return usolve[v]; }
   __device__ int plen(int64_t v) const { return (int)(pp[v + 1] - pp[v]); }
@@ -333,7 +341,7 @@ __device__ inline int exact_cmp_flag(const V &g, const UnitCtx &u, const SolveDe
     g.pent(u.v, jj, gs, k);
     same = target_y(tab, gs, k, la, ka) == target_y(tab, gs, k, lb, kb);
   }
-  if (!same) atomicOr(sd.redo + u.j, 1u);
+  if (!same) atomicMin(sd.redo + u.j, sd.mark);
   return Wa > Wb ? 1 : (Wa < Wb ? -1 : 0);
 }
 
@@ -733,100 +741,30 @@ struct LmCounters {
   unsigned long long *c;
 };
 
-// Candidates of one unit shared by B blocks (latency mode, units spanning several slices with
-// many candidates): each block builds the unit's whole table, evaluates the heaviest candidate
-// (it seeds pruning) and the candidates whose label hashes to its part, and publishes its
-// best; the block that finishes last reduces the B bests in the same total order (value, then
-// label) and decides.  The result is the one a single block reaches.
-struct CandSplit {
-  int part = 0, B = 1;
-  uint16_t *L2 = nullptr;   // LDS list of this block's candidate slots
-  int *n2 = nullptr;
-  ScoreK *parts = nullptr;  // [B] published bests of this unit
-  uint32_t *done = nullptr; // blocks of this unit finished (the last one resets it to 0)
-  int *last = nullptr;      // LDS: this block reduces
-  __device__ bool mine(uint32_t lab) const {
-    return (int)(((uint64_t)(lab * 2654435769u) * (uint32_t)B) >> 32) == part;
-  }
-};
-
-// This block's list of its own candidates (B > 1), else the table itself.
-template <class Grp, class Tab>
-__device__ inline Tab split_view(Grp grp, const Tab &tab, const CandSplit &cs) {
-  Tab ctab = tab;
-  if constexpr (std::is_same<Tab, LdsTab>::value) {
-    if (cs.B > 1) {
-      const int r = grp.rank(), gsz = grp.size();
-      if (r == 0) *cs.n2 = 0;
-      grp.sync();
-      const int nc = tab.count();
-      for (int i = r; i < nc; i += gsz) {
-        const int h = tab.slot(i);
-        const uint32_t key = tab.K[h];
-        if (key != 0 && cs.mine(key - 1)) cs.L2[atomicAdd(cs.n2, 1)] = (uint16_t)h;
-      }
-      grp.sync();
-      ctab.L = cs.L2;
-      ctab.n = cs.n2;
-    }
-  }
-  return ctab;
-}
-
-// Publish this block's best; true in the block that finishes last, whose `best` is then the
-// best over all B blocks.
-template <class P, class V, class Grp>
-__device__ inline bool split_reduce(Grp grp, const V &g, const UnitCtx &u, const SolveDev &sd,
-                                    const SliceTable &sig, const CandSplit &cs,
-                                    typename P::Score &best) {
-  if constexpr (std::is_same<typename P::Score, ScoreK>::value) {
-    if (grp.rank() == 0) {
-      cs.parts[cs.part] = best;
-      __threadfence();
-      const uint32_t old = atomicAdd(cs.done, 1u);
-      *cs.last = old == (uint32_t)(cs.B - 1);
-    }
-    grp.sync();
-    const bool last = *cs.last != 0;
-    grp.sync();
-    if (!last) return false;
-    __threadfence();
-    for (int i = 0; i < cs.B; i++) {
-      const ScoreK o = cs.parts[i];
-      if (better<P>(g, u, sd, sig, o, best)) best = o;
-    }
-    if (grp.rank() == 0) *cs.done = 0;
-    return true;
-  } else {
-    return true;
-  }
-}
-
 template <class P, class Grp, class Tab, class V>
 __device__ inline uint32_t lm_unit_coop(Grp grp, Tab tab, const V &g, const SolveDev &sd,
                                         const UnitCtx &u, const SliceTable &sig,
                                         uint32_t fresh_base, typename P::Score *red,
                                         LmCounters pc, typename P::Score best, int64_t hW,
-                                        uint32_t hL, const CandSplit &cs) {
+                                        uint32_t hL) {
   const int r = grp.rank(), gsz = grp.size();
   const CoopLane c = coop_lane(g, u, sd, sig, r);
-  const Tab ctab = split_view(grp, tab, cs);
   const int sub = r / c.mp, nsub = gsz / c.mp;
   int ncand = 0;
   if (hL != kNone) {
     ScoreK s = coop_make(u, c, hL, hW, kTarget);
     if (better<P>(g, u, sd, sig, s, best)) best = s;
-    ncand = r == 0 && cs.part == 0;
+    ncand = r == 0;
   }
   // subgroups take table slots kCoopBatch at a time; every lane runs the same turns
-  const int nc = ctab.count();
+  const int nc = tab.count();
   for (int i0 = 0; i0 < nc; i0 += nsub * kCoopBatch) {
     uint32_t lab[kCoopBatch];
     int64_t W[kCoopBatch], y[kCoopBatch];
     bool ok[kCoopBatch];
     for (int k = 0; k < kCoopBatch; k++) {
       const int i = i0 + k * nsub + sub;
-      const int h = i < nc ? ctab.slot(i) : 0;
+      const int h = i < nc ? tab.slot(i) : 0;
       const uint32_t key = i < nc ? tab.K[h] : 0u;
       lab[k] = key - 1;
       ok[k] = key != 0 && key - 1 != u.D && key - 1 != hL;
@@ -843,13 +781,12 @@ __device__ inline uint32_t lm_unit_coop(Grp grp, Tab tab, const V &g, const Solv
   }
   if (pc.c) {
     if (ncand) atomicAdd(pc.c + 2, (unsigned long long)ncand);
-    if (r == 0 && cs.part == 0) {
+    if (r == 0) {
       atomicAdd(pc.c + 0, 1ull);
       atomicAdd(pc.c + 1, (unsigned long long)g.degree(u.v));
     }
   }
   best = group_best<P>(grp, g, u, sd, sig, best, red);
-  if (cs.B > 1 && !split_reduce<P>(grp, g, u, sd, sig, cs, best)) return kNone;
   const int64_t wD = tab.get(u.D);
   const ScoreK stay = coop_make(u, c, u.D, wD, kStay);
   uint32_t out = kNone;
@@ -863,12 +800,9 @@ template <class P, class V, class Grp, class Tab>
 __device__ inline uint32_t lm_unit(Grp grp, Tab tab, const V &g, const SolveDev &sd, int64_t v,
                                    const uint32_t *comm, const SliceTable &sig, uint32_t fresh_base,
                                    typename P::Score *red, LmCounters pc, int64_t *sredW = nullptr,
-                                   uint32_t *sredL = nullptr, const CandSplit &cs = CandSplit()) {
+                                   uint32_t *sredL = nullptr) {
   const int r = grp.rank(), gsz = grp.size();
-  if (sd.frozen && sd.frozen[g.solve_of(v)]) {   // its solve is out of this sweep
-    if (cs.B > 1 && r == 0) *cs.last = 0;
-    return kNone;
-  }
+  if (sd.frozen && sd.frozen[g.solve_of(v)]) return kNone;   // its solve is out of this sweep
   for (int i = r; i < tab.size(); i += gsz) {
     tab.K[i] = 0;
     tab.V[i] = 0;
@@ -903,18 +837,17 @@ __device__ inline uint32_t lm_unit(Grp grp, Tab tab, const V &g, const SolveDev 
   group_heaviest(grp, tab, D, (const uint8_t *)nullptr, hW, hL, sredW, sredL);
   if constexpr (!V::kLevel0 && IsMulti<P>::value) {
     if (u.m >= kCoopMinM)
-      return lm_unit_coop<P>(grp, tab, g, sd, u, sig, fresh_base, red, pc, best, hW, hL, cs);
+      return lm_unit_coop<P>(grp, tab, g, sd, u, sig, fresh_base, red, pc, best, hW, hL);
   }
   int ncand = 0;
   if (hL != kNone) {
     typename P::Score s = P::make(g, u, sd, sig, hL, hW, kTarget);
     if (better<P>(g, u, sd, sig, s, best)) best = s;
-    ncand = r == 0 && cs.part == 0;
+    ncand = r == 0;
   }
-  const Tab ctab = split_view(grp, tab, cs);
-  const int nc = ctab.count();
+  const int nc = tab.count();
   for (int i = r; i < nc; i += gsz) {
-    const int h = ctab.slot(i);
+    const int h = tab.slot(i);
     uint32_t key = tab.K[h];
     if (key == 0 || key - 1 == D || key - 1 == hL) continue;
     if (P::prunable(u, tab.V[h], best)) continue;
@@ -924,16 +857,12 @@ __device__ inline uint32_t lm_unit(Grp grp, Tab tab, const V &g, const SolveDev 
   }
   if (pc.c) {
     if (ncand) atomicAdd(pc.c + 2, (unsigned long long)ncand);
-    if (r == 0 && cs.part == 0) {
+    if (r == 0) {
       atomicAdd(pc.c + 0, 1ull);
       atomicAdd(pc.c + 1, (unsigned long long)(row.hi - row.lo));
     }
   }
   best = group_best<P>(grp, g, u, sd, sig, best, red);
-  if (cs.B > 1 && !split_reduce<P>(grp, g, u, sd, sig, cs, best)) {
-    grp.sync();
-    return kNone;
-  }
   int64_t wD = tab.get(D);
   typename P::Score stay = P::make(g, u, sd, sig, D, wD, kStay);
   uint32_t out = kNone;
@@ -970,11 +899,9 @@ __host__ __device__ inline uint32_t degree_bin(int64_t d) {
 // (bin_fits checks that on the host before the first solve).
 __host__ __device__ inline uint32_t bin_of(int64_t d, int m) {
   if (m < kCoopMinM) return degree_bin(d);
-  const int64_t work = d * coop_width(m);
   if (d > kBlockMaxDeg) return 7u;
-  if (d <= kWaveMaxDeg && work <= 64 * 64) return 4u;
-  if (d <= kSmallBlockMaxDeg && work <= 256 * 64) return 5u;
-  return 6u;
+  if (d <= kWaveMaxDeg && d * coop_width(m) <= 64 * 64) return 4u;
+  return d <= kSmallBlockMaxDeg ? 5u : 6u;
 }
 __host__ __device__ inline bool bin_fits(int64_t d, uint32_t bin) {
   const int64_t cap[kNumBins] = {4, 8, 16, 32, kWaveMaxDeg, kSmallBlockMaxDeg, kBlockMaxDeg,
@@ -990,22 +917,40 @@ __device__ inline uint32_t batch_slot(const ViewK &g, int64_t v) {
   return unit_bin(g, v) + (g.plen(v) <= 1 ? (uint32_t)kNumBins : 0u);
 }
 
+// Where a decision goes: the target of its position and, when it is a move, the smallest moving
+// colour of the window (the stored value only falls, so a look before the atomic drops nearly
+// all of them).
+struct Emit {
+  uint32_t *target;
+  int32_t *first_move;
+  int32_t colour;
+  __device__ void put(int64_t pos, uint32_t out) const {
+    target[pos] = out;
+    if (out != kNone &&
+        __hip_atomic_load(first_move, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > colour)
+      atomicMin(first_move, colour);
+  }
+};
+
 // Units of degree <= G: G lanes per unit, one adjacency entry per lane; the group merges
 // equal community labels in a 2G-slot LDS table per group (the lane that claims a label's slot
 // leads it), every leader evaluates its community, and the group reduces to the best.  lk/lv:
 // the block's LDS, 128 slots per wave.
 template <class P, class V, int G>
 __device__ inline void lm_group_block(const V &g, const SolveDev &sd, const int32_t *units,
-                                      int64_t count, const uint32_t *comm, const SliceTable &sig,
-                                      uint32_t *target, uint32_t fresh_base, LmCounters pc,
-                                      int64_t blk, uint32_t *lk, int64_t *lv) {
+                                      int64_t pos, int count, const uint32_t *comm,
+                                      const SliceTable &sig, const Emit &em, uint32_t fresh_base,
+                                      LmCounters pc, uint32_t *lk, int64_t *lv) {
   const int lane = threadIdx.x & 63;
   const int gl = lane & (G - 1);
   const int gbase = lane & ~(G - 1);
-  const int64_t idx = (blk * blockDim.x + threadIdx.x) / G;
+  const int idx = threadIdx.x / G;
   if (idx >= count) return;   // whole groups leave together; shuffles stay inside a group
-  const int64_t v = units[idx];
-  if (sd.frozen && sd.frozen[g.solve_of(v)]) return;   // its solve is out of this sweep
+  const int64_t v = g.unit_at(units, pos + idx);
+  if (sd.frozen && sd.frozen[g.solve_of(v)]) {   // its solve is out of this sweep
+    if (gl == 0) em.target[pos + idx] = kNone;
+    return;
+  }
   const uint32_t D = comm[v];
   typename V::Row row = g.row(v, sd);
   UnitCtx u = unit_ctx(g, sd, v, D);
@@ -1090,7 +1035,7 @@ __device__ inline void lm_group_block(const V &g, const SolveDev &sd, const int3
     uint32_t out = kNone;
     if (P::cmp(g, u, sd, sig, best, stay) > 0)
       out = best.lab == kNone ? fresh_of(sd, fresh_base) + (uint32_t)g.orig(v) : best.lab;
-    target[idx] = out;
+    em.put(pos + idx, out);
   }
 }
 
@@ -1132,21 +1077,20 @@ struct SubTab {
 // order).
 template <int G, int U, bool kOne, bool kCopy>
 __device__ inline void lm0_lockstep(const ViewP &g, const SolveDev &sd, int64_t first,
-                                    int64_t count, const uint32_t *comm, const SliceTable &sig,
-                                    uint32_t *target, uint32_t fresh_base, LmCounters pc,
-                                    int64_t blk, uint32_t *lm0_keys,
-                                    unsigned long long *lm0_vals) {
+                                    int count, const uint32_t *comm, const SliceTable &sig,
+                                    const Emit &em, uint32_t fresh_base, LmCounters pc,
+                                    uint32_t *lm0_keys, unsigned long long *lm0_vals) {
   constexpr int kGroups = 256 / G;
   const int lane = threadIdx.x & 63;
   const int gl = lane & (G - 1);
   const int gbase = lane & ~(G - 1);
-  const int64_t base = blk * (int64_t)(kGroups * U) + threadIdx.x / G;
+  const int base = threadIdx.x / G;
   if (base >= count) return;   // whole groups leave together
   int64_t pos[U];
   bool live[U];
 #pragma unroll
   for (int u = 0; u < U; u++) {
-    const int64_t i = base + (int64_t)u * kGroups;
+    const int i = base + u * kGroups;
     live[u] = i < count;
     pos[u] = first + (live[u] ? i : 0);
   }
@@ -1164,6 +1108,7 @@ __device__ inline void lm0_lockstep(const ViewP &g, const SolveDev &sd, int64_t 
     gs[u] = g.slice[v];
     js[u] = kOne ? 0 : g.solve_of(v);   // one solve: its constants are uniform
     if (sd.frozen && sd.frozen[js[u]]) {   // a solve out of this sweep: nothing to decide
+      if (live[u] && gl == 0) em.target[pos[u]] = kNone;
       live[u] = false;
       hi[u] = lo[u];
     }
@@ -1321,344 +1266,332 @@ __device__ inline void lm0_lockstep(const ViewP &g, const SolveDev &sd, int64_t 
       uint32_t out = kNone;
       if (best.g > stay)
         out = best.lab == kNone ? fresh_of(sd, fresh_base) + (uint32_t)g.uid[pos[u]] : best.lab;
-      target[pos[u] - first] = out;
+      em.put(pos[u], out);
     }
     (void)p;
   }
 }
 
-template <class P, class V, int G>
-__global__ __launch_bounds__(256) void k_lm_group(V g, SolveDev sd, const int32_t *units,
-                                                  int64_t count, const uint32_t *comm,
-                                                  SliceTable sig, uint32_t *target,
-                                                  uint32_t fresh_base, LmCounters pc) {
-  __shared__ uint32_t lk[4 * 128];
-  __shared__ int64_t lv[4 * 128];
-  lm_group_block<P, V, G>(g, sd, units, count, comm, sig, target, fresh_base, pc, blockIdx.x, lk,
-                          lv);
-}
+// ------------------------------------------------------------------ colour windows
+// A sweep visits the colours one after another: the units of a colour decide together, their
+// moves are applied, the next colour follows.  Past a level's first sweeps most colours move
+// nothing (1215 of 8158 aggregated-level batches of a 3.2M-copy solve, 68 of 1082 of a warm
+// start), so a window of consecutive colours is decided at once from the state before it.  The
+// decisions of the colours up to and including the first one that moves are those of the
+// colour-by-colour sweep (nothing moved before them); that colour's moves are applied and the
+// next window starts behind it, so every move is the one the sweep makes.  The window is kept
+// on the device: decision kernels read it, the apply kernel writes the next one, and the host
+// queues pairs of both without waiting; a pair that comes after the last colour does nothing.
+//
+// Work is cut into items of one block each, listed per kernel family in colour order.
+enum { kFamGroup1, kFamGroup, kFamMulti1, kFamMulti, kFamBlock, kFamHub, kFams };
 
-template <class P, class V>
-__global__ __launch_bounds__(256) void k_lm_wave(V g, SolveDev sd, const int32_t *units,
-                                                 int64_t count, const uint32_t *comm,
-                                                 SliceTable sig, uint32_t *target,
-                                                 uint32_t fresh_base, LmCounters pc) {
-  __shared__ uint32_t sk[4][1 << kWaveLg];
-  __shared__ int64_t sv[4][1 << kWaveLg];
-  __shared__ uint16_t sl[4][kWaveMaxDeg];
-  __shared__ int sn[4];
-  const int wv = threadIdx.x >> 6;
-  const int64_t idx = (int64_t)blockIdx.x * 4 + wv;
-  if (idx >= count) return;
-  LdsTab tab{sk[wv], sv[wv], kWaveLg, sl[wv], sn + wv};
-  uint32_t t = lm_unit<P>(WaveGrp(), tab, g, sd, units[idx], comm, sig, fresh_base,
-                          (typename P::Score *)nullptr, pc);
-  if ((threadIdx.x & 63) == 0) target[idx] = t;
-}
+struct WinItem {
+  int32_t pos, count;   // positions [pos, pos + count) of the colour order
+  int32_t slot;         // batch slot (class and degree bin) the block's code follows
+  int32_t colour;
+};
+struct WinSeg {         // one (colour, slot) run of units, cut into items of `per` units
+  int32_t item0, items, pos, count, per, slot, colour, pad;
+};
+struct WinState {
+  int32_t c0, c1;       // the window; empty once every colour has been visited
+  int32_t budget;       // blocks of work the next window may hold
+  int32_t windows;      // windows decided in this sweep
+  int32_t t;            // the sweep
+};
+struct WinLevel {
+  const WinItem *items;
+  const int32_t *ip;    // [kFams][ncol + 1] first item of each colour
+  const int32_t *cost;  // [ncol + 1] blocks of work before each colour
+  const int32_t *cptr;  // [ncol + 1] first position of each colour
+  int32_t *moved_at;    // [ncol] last sweep in which the colour moved
+  WinState *st;         // [3] ring: pair r uses r % 3
+  int32_t *first_move;  // [3] smallest moving colour of the pair's window
+  int32_t *near_tie;    // [3][J] smallest colour of each solve with an unsettled near-tie
+  int32_t ncol, floor, J;
+};
+constexpr int32_t kNoColour = 0x7fffffff;
+constexpr int kXcds = 8;   // MI355X: eight accelerator complex dies, each with its own L2
 
-template <class P, class V, int NT, int LG>
-__global__ __launch_bounds__(NT) void k_lm_block(V g, SolveDev sd, const int32_t *units,
-                                                 int64_t count, const uint32_t *comm,
-                                                 SliceTable sig, uint32_t *target,
-                                                 uint32_t fresh_base, LmCounters pc) {
-  __shared__ uint32_t sk[1 << LG];
-  __shared__ int64_t sv[1 << LG];
-  __shared__ uint16_t sl[1 << (LG - 1)];   // degree bound of the bin: half the table
-  __shared__ int sn;
-  __shared__ typename P::Score red[NT / 64];
-  __shared__ int64_t hw[NT / 64];
-  __shared__ uint32_t hl[NT / 64];
-  LdsTab tab{sk, sv, LG, sl, &sn};
-  for (int64_t idx = blockIdx.x; idx < count; idx += gridDim.x) {
-    uint32_t t = lm_unit<P>(BlockGrp(), tab, g, sd, units[idx], comm, sig, fresh_base, red, pc,
-                            hw, hl);
-    if (threadIdx.x == 0) target[idx] = t;
+__global__ __launch_bounds__(256) void k_win_items(const WinSeg *segs, WinItem *items) {
+  const WinSeg s = segs[blockIdx.x];
+  for (int i = threadIdx.x; i < s.items; i += blockDim.x) {
+    const int left = s.count - i * s.per;
+    items[s.item0 + i] = WinItem{s.pos + i * s.per, left < s.per ? left : s.per, s.slot, s.colour};
   }
 }
 
-// Bins 0..5 of one colour batch in one launch: consecutive block ranges per bin, each block
-// running that bin's code (fewer launches and no per-bin tail).
-struct BinSeg {
-  const int32_t *units;
-  uint32_t *target;
-  int64_t count;
-  int64_t blk0;     // first block of the segment
-  int64_t nbk;      // blocks with work (k_lm_multi: the segment spans nbk rounded up to kXcds)
-  int64_t first;    // level 0 in position order: position of the segment's first unit
-  int32_t parts;    // latency mode: blocks per unit (candidates split, CandSplit)
-  int64_t poff;     // latency mode: the segment's first split-unit slot
+// Items of a family in pair r's window, in the order that gives each XCD a contiguous eighth of
+// them (blocks are dealt to the XCDs round-robin): units are in id order inside a batch, so an
+// XCD's L2 sees the labels and Sigma sub-tables of a few slices.
+struct WinRange {
+  int i0, n, per;
+  __device__ WinRange(const WinLevel &L, int fam, int r) {
+    const WinState s = L.st[r];
+    const int32_t *ip = L.ip + fam * (L.ncol + 1);
+    i0 = s.c0 < s.c1 ? ip[s.c0] : 0;
+    n = s.c0 < s.c1 ? ip[s.c1] - i0 : 0;
+    per = (n + kXcds - 1) / kXcds;
+  }
+  __device__ int turns() const { return per * kXcds; }
+  // item of turn k, -1 when the turn has none
+  __device__ int item(int k) const {
+    const int i = (k % kXcds) * per + k / kXcds;
+    return i < n ? i0 + i : -1;
+  }
 };
-struct MultiSeg {
-  BinSeg s[6];
-  int64_t nblk;     // blocks with work (the grid is rounded up to a multiple of kXcds)
-};
-constexpr int kXcds = 8;   // MI355X: eight accelerator complex dies, each with its own L2
 
+// Window from colour c0 on (one wave): as many colours as the budget holds, at least one, up to
+// and including the next colour that moved in the last sweep (it will probably move again, and
+// what lies behind it would be decided twice); below `floor` blocks the chip is not full and
+// deciding further ahead costs nothing.
+__device__ inline int win_end(const WinLevel &L, int t, int c0, int budget) {
+  const int lane = threadIdx.x & 63;
+  const int lim = budget > L.floor ? budget : L.floor;
+  int c1 = c0;
+  const int base = c0 < L.ncol ? L.cost[c0] : 0;
+  while (c1 < L.ncol) {
+    const int c = c1 + lane;
+    const int cost = c < L.ncol ? L.cost[c + 1] - base : 0;
+    const bool in = c < L.ncol && (c == c0 || cost <= lim);
+    const bool stop = in && cost > L.floor && L.moved_at[c] >= t - 1;
+    const uint64_t out = ~__ballot(in), stops = __ballot(stop);
+    const int n_in = out ? __builtin_ctzll(out) : 64;
+    const int n_stop = stops ? __builtin_ctzll(stops) + 1 : 64;
+    const int take = n_in < n_stop ? n_in : n_stop;
+    c1 += take;
+    if (take < 64) break;
+  }
+  return c1;
+}
+
+constexpr int32_t kWinUnbounded = 1 << 28;
+
+// Start of sweep t (one block): first window, cleared counters.  The first sweep of a level
+// starts with a narrow window; later ones are led by what moved in the sweep before.
+__global__ __launch_bounds__(256) void k_win_begin(WinLevel L, int t, uint32_t *moved,
+                                                   int32_t *redo, int *flag) {
+  for (int i = threadIdx.x; i < L.J; i += blockDim.x) {
+    moved[i] = 0;
+    redo[i] = kRedoUnset;
+    if (L.near_tie)
+      for (int k = 0; k < 3; k++) L.near_tie[k * L.J + i] = kNoColour;
+  }
+  if (threadIdx.x == 0) *flag = 0;
+  if (threadIdx.x < 3) L.first_move[threadIdx.x] = kNoColour;
+  if (threadIdx.x < 64) {
+    const int budget = t == 0 ? L.floor : kWinUnbounded;
+    const int c1 = win_end(L, t, 0, budget);
+    if (threadIdx.x == 0) L.st[0] = WinState{0, c1, budget, 0, t};
+  }
+}
+
+// One block's share of a unit bin: lane groups, waves or the whole block (bins 0..5).
 template <class P, class V>
-__global__ __launch_bounds__(256) void k_lm_multi(V g, SolveDev sd, MultiSeg ms,
-                                                  const uint32_t *comm, SliceTable sig,
-                                                  uint32_t fresh_base, LmCounters pc) {
+__device__ inline void win_item(const V &g, const SolveDev &sd, const int32_t *units,
+                                const WinItem &it, const uint32_t *comm, const SliceTable &sig,
+                                const Emit &em, uint32_t fresh_base, LmCounters pc, uint32_t *sk,
+                                int64_t *sv, uint16_t *sl, int *sn, typename P::Score *red,
+                                int64_t *hw, uint32_t *hl) {
+  switch (it.slot % kNumBins) {
+    case 0:
+      lm_group_block<P, V, 4>(g, sd, units, it.pos, it.count, comm, sig, em, fresh_base, pc, sk, sv);
+      break;
+    case 1:
+      lm_group_block<P, V, 8>(g, sd, units, it.pos, it.count, comm, sig, em, fresh_base, pc, sk, sv);
+      break;
+    case 2:
+      lm_group_block<P, V, 16>(g, sd, units, it.pos, it.count, comm, sig, em, fresh_base, pc, sk,
+                               sv);
+      break;
+    case 3:
+      lm_group_block<P, V, 32>(g, sd, units, it.pos, it.count, comm, sig, em, fresh_base, pc, sk,
+                               sv);
+      break;
+    case 4: {
+      const int wv = threadIdx.x >> 6;
+      if (wv >= it.count) break;
+      // a unit of at most 64 entries in fewer than kCoopMinM slices: the wave as one lane group
+      // (entries one per lane, labels merged in this wave's LDS region)
+      const int64_t v = g.unit_at(units, it.pos + wv);
+      if (g.degree(v) <= 64 && g.plen(v) < kCoopMinM) {
+        // lm_group_block addresses 128 slots per wave from the pointer it gets: shift it so
+        // that this wave lands on its own 512-slot wave table, which no other wave touches
+        lm_group_block<P, V, 64>(g, sd, units, it.pos, it.count, comm, sig, em, fresh_base, pc,
+                                 sk + (wv << kWaveLg) - wv * 128, sv + (wv << kWaveLg) - wv * 128);
+        break;
+      }
+      LdsTab tab{sk + (wv << kWaveLg), sv + (wv << kWaveLg), kWaveLg, sl + wv * kWaveMaxDeg,
+                 sn + wv};
+      const uint32_t out = lm_unit<P>(WaveGrp(), tab, g, sd, v, comm, sig, fresh_base,
+                                      (typename P::Score *)nullptr, pc);
+      if ((threadIdx.x & 63) == 0) em.put(it.pos + wv, out);
+      break;
+    }
+    default: {
+      LdsTab tab{sk, sv, kSmallBlockLg, sl, sn};
+      const uint32_t out = lm_unit<P>(BlockGrp(), tab, g, sd, g.unit_at(units, it.pos), comm, sig,
+                                      fresh_base, red, pc, hw, hl);
+      if (threadIdx.x == 0) em.put(it.pos, out);
+    }
+  }
+}
+
+// Bins 0..5 of a window: units of class 1 (slots from kNumBins on) by P1, the others by P.
+template <class P, class P1, class V>
+__global__ __launch_bounds__(256) void k_win_multi(V g, SolveDev sd, WinLevel L, int fam, int r,
+                                                   const int32_t *units, const uint32_t *comm,
+                                                   SliceTable sig, uint32_t *target,
+                                                   uint32_t fresh_base, LmCounters pc) {
   __shared__ uint32_t sk[1 << kSmallBlockLg];        // 4 wave tables of 512, or one of 2048
   __shared__ int64_t sv[1 << kSmallBlockLg];
   __shared__ uint16_t sl[kSmallBlockMaxDeg];         // 4 lists of 256, or one of 1024
   __shared__ int sn[4];
   __shared__ typename P::Score red[4];
+  __shared__ typename P1::Score red1[4];
   __shared__ int64_t hw[4];
   __shared__ uint32_t hl[4];
-  // XCD-aware order: workgroups are dealt to the 8 XCDs round-robin and every segment starts
-  // at a multiple of 8, so within a segment block p serves the (p % 8)-th eighth of the
-  // segment's units; units are in id (slice-major) order, so each XCD's L2 sees the labels
-  // and Sigma sub-tables of a few slices while every XCD gets an equal share of every bin
-  const int64_t b = blockIdx.x;
-  int k = 0;
-  while (k < 5 && b >= ms.s[k + 1].blk0) k++;
-  const BinSeg sg = ms.s[k];
-  const int64_t p = b - sg.blk0;
-  const int64_t per = (sg.nbk + kXcds - 1) / kXcds;
-  const int64_t lb = (p % kXcds) * per + p / kXcds;
-  if (lb >= sg.nbk) return;
-  switch (k) {
-    case 0:
-      lm_group_block<P, V, 4>(g, sd, sg.units, sg.count, comm, sig, sg.target, fresh_base, pc, lb,
-                               sk, sv);
-      break;
-    case 1:
-      lm_group_block<P, V, 8>(g, sd, sg.units, sg.count, comm, sig, sg.target, fresh_base, pc, lb,
-                               sk, sv);
-      break;
-    case 2:
-      lm_group_block<P, V, 16>(g, sd, sg.units, sg.count, comm, sig, sg.target, fresh_base, pc,
-                               lb, sk, sv);
-      break;
-    case 3:
-      lm_group_block<P, V, 32>(g, sd, sg.units, sg.count, comm, sig, sg.target, fresh_base, pc,
-                               lb, sk, sv);
-      break;
-    case 4: {
-      const int wv = threadIdx.x >> 6;
-      const int64_t idx = lb * 4 + wv;
-      if (idx >= sg.count) return;
-      // a unit of at most 64 entries in fewer than kCoopMinM slices: the wave as one lane group
-      // (entries one per lane, labels merged in this wave's LDS region)
-      const int64_t v0 = sg.units[idx];
-      if (g.degree(v0) <= 64 && g.plen(v0) < kCoopMinM) {
-        // lm_group_block addresses 128 slots per wave from the pointer it gets: shift it so
-        // that this wave lands on its own 512-slot wave table, which no other wave touches
-        lm_group_block<P, V, 64>(g, sd, sg.units, sg.count, comm, sig, sg.target, fresh_base, pc,
-                                 lb, sk + (wv << kWaveLg) - wv * 128,
-                                 sv + (wv << kWaveLg) - wv * 128);
-        break;
-      }
-      LdsTab tab{sk + (wv << kWaveLg), sv + (wv << kWaveLg), kWaveLg, sl + wv * kWaveMaxDeg,
-                 sn + wv};
-      uint32_t t = lm_unit<P>(WaveGrp(), tab, g, sd, sg.units[idx], comm, sig, fresh_base,
-                              (typename P::Score *)nullptr, pc);
-      if ((threadIdx.x & 63) == 0) sg.target[idx] = t;
-      break;
-    }
-    default: {
-      LdsTab tab{sk, sv, kSmallBlockLg, sl, sn};
-      uint32_t t = lm_unit<P>(BlockGrp(), tab, g, sd, sg.units[lb], comm, sig, fresh_base, red,
-                              pc, hw, hl);
-      if (threadIdx.x == 0) sg.target[lb] = t;
-    }
+  const WinRange w(L, fam, r);
+  if (sd.redo) sd.redo = L.near_tie + r * L.J;
+  for (int k = blockIdx.x; k < w.turns(); k += gridDim.x) {
+    const int i = w.item(k);
+    if (i < 0) continue;
+    const WinItem it = L.items[i];
+    const Emit em{target, L.first_move + r, it.colour};
+    sd.mark = it.colour;
+    if (!std::is_same<P, P1>::value && it.slot >= kNumBins)
+      win_item<P1>(g, sd, units, it, comm, sig, em, fresh_base, pc, sk, sv, sl, sn, red1, hw, hl);
+    else
+      win_item<P>(g, sd, units, it, comm, sig, em, fresh_base, pc, sk, sv, sl, sn, red, hw, hl);
+    __syncthreads();   // the next item lays its tables over this one's
   }
 }
 
-// Bins 0..3 alone (lane groups, one adjacency entry per lane): no LDS, so a large batch runs at
-// the occupancy the group code's registers allow, where the fused kernel's LDS tables would
-// hold it lower.  Same XCD-aware block order as k_lm_multi.
+// Bins 0..3 alone: little LDS, so large batches run at the occupancy the group code's registers
+// allow, where the fused kernel's tables would hold it lower.
 template <class P, class V>
-__global__ __launch_bounds__(256) void k_lm_groups(V g, SolveDev sd, MultiSeg ms,
-                                                   const uint32_t *comm, SliceTable sig,
-                                                   uint32_t fresh_base, LmCounters pc) {
+__global__ __launch_bounds__(256) void k_win_groups(V g, SolveDev sd, WinLevel L, int fam, int r,
+                                                    const int32_t *units, const uint32_t *comm,
+                                                    SliceTable sig, uint32_t *target,
+                                                    uint32_t fresh_base, LmCounters pc) {
   __shared__ uint32_t lk[4 * 128];
   __shared__ int64_t lv[4 * 128];
-  const int64_t b = blockIdx.x;
-  int k = 0;
-  while (k < 3 && b >= ms.s[k + 1].blk0) k++;
-  const BinSeg sg = ms.s[k];
-  const int64_t p = b - sg.blk0;
-  const int64_t per = (sg.nbk + kXcds - 1) / kXcds;
-  const int64_t lb = (p % kXcds) * per + p / kXcds;
-  if (lb >= sg.nbk) return;
-  switch (k) {
-    case 0:
-      lm_group_block<P, V, 4>(g, sd, sg.units, sg.count, comm, sig, sg.target, fresh_base, pc, lb,
-                               lk, lv);
-      break;
-    case 1:
-      lm_group_block<P, V, 8>(g, sd, sg.units, sg.count, comm, sig, sg.target, fresh_base, pc, lb,
-                               lk, lv);
-      break;
-    case 2:
-      lm_group_block<P, V, 16>(g, sd, sg.units, sg.count, comm, sig, sg.target, fresh_base, pc,
-                               lb, lk, lv);
-      break;
-    default:
-      lm_group_block<P, V, 32>(g, sd, sg.units, sg.count, comm, sig, sg.target, fresh_base, pc,
-                               lb, lk, lv);
-  }
-}
-
-// Bins 0..3 of a level-0 colour batch in position order (lm0_lockstep), XCD-aware block order
-// as in k_lm_multi; segment k starts at position ms.s[k].first.  kOne: a single solve; kCopy:
-// neighbour labels from the label copy.
-template <int U, bool kOne, bool kCopy>
-__global__ __launch_bounds__(256) void k_lm0_groups(ViewP g, SolveDev sd, MultiSeg ms,
-                                                    const uint32_t *comm, SliceTable sig,
-                                                    uint32_t fresh_base, LmCounters pc) {
-  __shared__ uint32_t keys[4 * U * 128];
-  __shared__ unsigned long long vals[4 * U * 128];
-  const int64_t b = blockIdx.x;
-  int k = 0;
-  while (k < 3 && b >= ms.s[k + 1].blk0) k++;
-  const BinSeg sg = ms.s[k];
-  const int64_t p = b - sg.blk0;
-  const int64_t per = (sg.nbk + kXcds - 1) / kXcds;
-  const int64_t lb = (p % kXcds) * per + p / kXcds;
-  if (lb >= sg.nbk) return;
-  switch (k) {
-    case 0:
-      lm0_lockstep<4, U, kOne, kCopy>(g, sd, sg.first, sg.count, comm, sig, sg.target,
-                                        fresh_base, pc, lb, keys, vals);
-      break;
-    case 1:
-      lm0_lockstep<8, U, kOne, kCopy>(g, sd, sg.first, sg.count, comm, sig, sg.target,
-                                        fresh_base, pc, lb, keys, vals);
-      break;
-    case 2:
-      lm0_lockstep<16, U, kOne, kCopy>(g, sd, sg.first, sg.count, comm, sig, sg.target,
-                                        fresh_base, pc, lb, keys, vals);
-      break;
-    default:
-      lm0_lockstep<32, U, kOne, kCopy>(g, sd, sg.first, sg.count, comm, sig, sg.target,
-                                        fresh_base, pc, lb, keys, vals);
-  }
-}
-
-// Latency mode (aggregated levels, colour batches of few units): every bin below the hub bin
-// of both unit classes in one launch.  Occupancy does not matter here, so one kernel carries
-// both policies and an LDS table large enough for degree 4096; its blocks have 512 threads,
-// which leaves the multi-slice policy the registers it needs without spilling.
-struct LatSegs {
-  BinSeg s[2 * kBinGtab];   // class (single-slice, multi-slice) x bins 0..kBinGtab-1
-  ScoreK *part;             // [split-unit slots x parts] published bests
-  uint32_t *done;           // [split-unit slots] finished blocks, 0 between launches
-};
-
-template <class P, class V>
-__device__ inline void lat_bin(const V &g, const SolveDev &sd, const BinSeg &sg, int bin,
-                               int64_t lb, const uint32_t *comm, const SliceTable &sig,
-                               uint32_t fresh_base, LmCounters pc, uint32_t *sk, int64_t *sv,
-                               uint16_t *sl, int *sn, typename P::Score *red, int64_t *hw,
-                               uint32_t *hl, CandSplit cs, ScoreK *ls_part, uint32_t *ls_done) {
-  switch (bin) {
-    case 0:
-      lm_group_block<P, V, 4>(g, sd, sg.units, sg.count, comm, sig, sg.target, fresh_base, pc, lb,
-                               sk, sv);
-      break;
-    case 1:
-      lm_group_block<P, V, 8>(g, sd, sg.units, sg.count, comm, sig, sg.target, fresh_base, pc, lb,
-                               sk, sv);
-      break;
-    case 2:
-      lm_group_block<P, V, 16>(g, sd, sg.units, sg.count, comm, sig, sg.target, fresh_base, pc,
-                               lb, sk, sv);
-      break;
-    case 3:
-      lm_group_block<P, V, 32>(g, sd, sg.units, sg.count, comm, sig, sg.target, fresh_base, pc,
-                               lb, sk, sv);
-      break;
-    default: {   // one unit per block, or sg.parts blocks per unit; table sized by the bin
-      const int lg = bin <= 5 ? kSmallBlockLg : kBlockLg;
-      LdsTab tab{sk, sv, lg, sl, sn};
-      const int64_t unit = lb / sg.parts;
-      if (sg.parts > 1) {
-        cs.part = (int)(lb % sg.parts);
-        cs.B = sg.parts;
-        cs.parts = ls_part + (sg.poff + unit) * sg.parts;
-        cs.done = ls_done + sg.poff + unit;
-      }
-      uint32_t t = lm_unit<P>(BlockGrp(), tab, g, sd, sg.units[unit], comm, sig, fresh_base, red,
-                              pc, hw, hl, cs);
-      if (threadIdx.x == 0 && (sg.parts == 1 || *cs.last)) sg.target[unit] = t;
+  const WinRange w(L, fam, r);
+  if (sd.redo) sd.redo = L.near_tie + r * L.J;
+  for (int k = blockIdx.x; k < w.turns(); k += gridDim.x) {
+    const int i = w.item(k);
+    if (i < 0) continue;
+    const WinItem it = L.items[i];
+    const Emit em{target, L.first_move + r, it.colour};
+    sd.mark = it.colour;
+    switch (it.slot % kNumBins) {
+      case 0:
+        lm_group_block<P, V, 4>(g, sd, units, it.pos, it.count, comm, sig, em, fresh_base, pc, lk,
+                                lv);
+        break;
+      case 1:
+        lm_group_block<P, V, 8>(g, sd, units, it.pos, it.count, comm, sig, em, fresh_base, pc, lk,
+                                lv);
+        break;
+      case 2:
+        lm_group_block<P, V, 16>(g, sd, units, it.pos, it.count, comm, sig, em, fresh_base, pc, lk,
+                                 lv);
+        break;
+      default:
+        lm_group_block<P, V, 32>(g, sd, units, it.pos, it.count, comm, sig, em, fresh_base, pc, lk,
+                                 lv);
     }
   }
 }
 
-constexpr int kLatThreads = 512;
-// Block size of the 8192-slot table kernels: the multi-slice policy needs more than the 128
-// registers per lane that 1024-thread blocks allow
+// Bins 0..3 of level 0 in position order (lm0_lockstep).  kOne: a single solve; kCopy:
+// neighbour labels from the label copy.
+template <int U, bool kOne, bool kCopy>
+__global__ __launch_bounds__(256) void k_win_lm0(ViewP g, SolveDev sd, WinLevel L, int r,
+                                                 const uint32_t *comm, SliceTable sig,
+                                                 uint32_t *target, uint32_t fresh_base,
+                                                 LmCounters pc) {
+  __shared__ uint32_t keys[4 * U * 128];
+  __shared__ unsigned long long vals[4 * U * 128];
+  const WinRange w(L, kFamGroup, r);
+  for (int k = blockIdx.x; k < w.turns(); k += gridDim.x) {
+    const int i = w.item(k);
+    if (i < 0) continue;
+    const WinItem it = L.items[i];
+    const Emit em{target, L.first_move + r, it.colour};
+    switch (it.slot) {
+      case 0:
+        lm0_lockstep<4, U, kOne, kCopy>(g, sd, it.pos, it.count, comm, sig, em, fresh_base, pc,
+                                        keys, vals);
+        break;
+      case 1:
+        lm0_lockstep<8, U, kOne, kCopy>(g, sd, it.pos, it.count, comm, sig, em, fresh_base, pc,
+                                        keys, vals);
+        break;
+      case 2:
+        lm0_lockstep<16, U, kOne, kCopy>(g, sd, it.pos, it.count, comm, sig, em, fresh_base, pc,
+                                         keys, vals);
+        break;
+      default:
+        lm0_lockstep<32, U, kOne, kCopy>(g, sd, it.pos, it.count, comm, sig, em, fresh_base, pc,
+                                         keys, vals);
+    }
+  }
+}
+
+// Bin 6: one block per unit, a table for up to kBlockMaxDeg distinct labels.  The multi-slice
+// policy needs more than the 128 registers per lane that 1024-thread blocks allow.
 template <class P>
 constexpr int kBlockThreads = IsMulti<P>::value ? 512 : 1024;
 
-template <class V, class PK>
-__global__ __launch_bounds__(kLatThreads) void k_lm_lat(V g, SolveDev sd, LatSegs ls,
-                                                        const uint32_t *comm, SliceTable sig,
-                                                        uint32_t fresh_base, LmCounters pc) {
+template <class P, class V, int NT>
+__global__ __launch_bounds__(NT) void k_win_block(V g, SolveDev sd, WinLevel L, int r,
+                                                  const int32_t *units, const uint32_t *comm,
+                                                  SliceTable sig, uint32_t *target,
+                                                  uint32_t fresh_base, LmCounters pc) {
   __shared__ uint32_t sk[1 << kBlockLg];
   __shared__ int64_t sv[1 << kBlockLg];
   __shared__ uint16_t sl[kBlockMaxDeg];
   __shared__ int sn;
-  __shared__ ScoreK redK[kLatThreads / 64];
-  __shared__ Score1 red1[kLatThreads / 64];
-  __shared__ int64_t hw[kLatThreads / 64];
-  __shared__ uint32_t hl[kLatThreads / 64];
-  __shared__ uint16_t sl2[kBlockMaxDeg];
-  __shared__ int sn2, slast;
-  const int64_t b = blockIdx.x;
-  int k = 0;
-  while (k < 2 * kBinGtab - 1 && b >= ls.s[k + 1].blk0) k++;
-  const BinSeg sg = ls.s[k];
-  const int64_t lb = b - sg.blk0;
-  const int bin = k % kBinGtab;
-  CandSplit cs;
-  cs.L2 = sl2;
-  cs.n2 = &sn2;
-  cs.last = &slast;
-  if (k < kBinGtab)
-    lat_bin<PolicyK1>(g, sd, sg, bin, lb, comm, sig, fresh_base, pc, sk, sv, sl, &sn, red1, hw,
-                      hl, cs, ls.part, ls.done);
-  else
-    lat_bin<PK>(g, sd, sg, bin, lb, comm, sig, fresh_base, pc, sk, sv, sl, &sn, redK, hw, hl, cs,
-                ls.part, ls.done);
-}
-
-// Units of very high degree: a global-memory table per unit, slot offsets from a scan.
-template <class P, class V>
-__global__ __launch_bounds__(256) void k_lm_gtab(V g, SolveDev sd, const int32_t *units,
-                                                 int64_t count, const uint32_t *comm,
-                                                 SliceTable sig, uint32_t *target,
-                                                 uint32_t fresh_base, uint32_t *gk, int64_t *gv,
-                                                 const int64_t *goff, const int32_t *glg,
-                                                 LmCounters pc) {
-  __shared__ typename P::Score red[4];
-  __shared__ int64_t hw[4];
-  __shared__ uint32_t hl[4];
-  for (int64_t idx = blockIdx.x; idx < count; idx += gridDim.x) {
-    const int64_t v = units[idx];
-    GTab tab{gk + goff[v], gv + goff[v], glg[v]};
-    uint32_t t = lm_unit<P>(BlockGrpG(), tab, g, sd, v, comm, sig, fresh_base, red, pc, hw, hl);
-    if (threadIdx.x == 0) target[idx] = t;
+  __shared__ typename P::Score red[NT / 64];
+  __shared__ int64_t hw[NT / 64];
+  __shared__ uint32_t hl[NT / 64];
+  LdsTab tab{sk, sv, kBlockLg, sl, &sn};
+  const WinRange w(L, kFamBlock, r);
+  if (sd.redo) sd.redo = L.near_tie + r * L.J;
+  for (int k = blockIdx.x; k < w.turns(); k += gridDim.x) {
+    const int i = w.item(k);
+    if (i < 0) continue;
+    const WinItem it = L.items[i];
+    sd.mark = it.colour;
+    const uint32_t out = lm_unit<P>(BlockGrp(), tab, g, sd, g.unit_at(units, it.pos), comm, sig,
+                                    fresh_base, red, pc, hw, hl);
+    if (threadIdx.x == 0) Emit{target, L.first_move + r, it.colour}.put(it.pos, out);
+    __syncthreads();
   }
 }
 
 // ------------------------------------------------------------------ hub units
 // Units above the block bins are spread over kHubBlocks blocks each (grid = kHubBlocks x
-// units): the blocks clear, fill and scan disjoint parts of the unit's global table, each
+// window's hubs): the blocks clear, fill and scan disjoint parts of the unit's global table, each
 // scan keeps its best candidate, and one wave per unit reduces those with the same total
 // order (value, then label) and compares with staying.  The result equals one group's.
 constexpr int kHubBlocks = 16;
 
-__global__ __launch_bounds__(256) void k_hub_clear(const int32_t *units, const int64_t *goff,
-                                                   const int32_t *glg, uint32_t *gk, int64_t *gv) {
-  const int64_t v = units[blockIdx.y];
-  const int64_t size = 1ll << glg[v], base = goff[v];
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < size;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    gk[base + i] = 0;
-    gv[base + i] = 0;
+template <class V>
+__global__ __launch_bounds__(256) void k_hub_clear(V g, WinLevel L, int r, const int32_t *units,
+                                                   const int64_t *goff, const int32_t *glg,
+                                                   uint32_t *gk, int64_t *gv) {
+  const WinRange w(L, kFamHub, r);
+  for (int y = blockIdx.y; y < w.n; y += gridDim.y) {
+    const int64_t v = g.unit_at(units, L.items[w.i0 + y].pos);
+    const int64_t size = 1ll << glg[v], base = goff[v];
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < size;
+         i += (int64_t)gridDim.x * blockDim.x) {
+      gk[base + i] = 0;
+      gv[base + i] = 0;
+    }
   }
 }
 
@@ -1670,198 +1603,280 @@ constexpr int kHubLdsLg = 11;
 constexpr int kHubLdsKeys = 1 << (kHubLdsLg - 1);
 
 template <class V>
-__global__ __launch_bounds__(256) void k_hub_accum(V g, SolveDev sd, const int32_t *units,
-                                                   const uint32_t *comm, const int64_t *goff,
-                                                   const int32_t *glg, uint32_t *gk, int64_t *gv,
-                                                   LmCounters pc) {
+__global__ __launch_bounds__(256) void k_hub_accum(V g, SolveDev sd, WinLevel L, int r,
+                                                   const int32_t *units, const uint32_t *comm,
+                                                   const int64_t *goff, const int32_t *glg,
+                                                   uint32_t *gk, int64_t *gv, LmCounters pc) {
   __shared__ uint32_t sk[1 << kHubLdsLg];
   __shared__ int64_t sv[1 << kHubLdsLg];
   __shared__ int s_claimed;
-  const int64_t v = units[blockIdx.y];
-  GTab tab{gk + goff[v], gv + goff[v], glg[v]};
-  typename V::Row row = g.row(v, sd);
-  for (int i = threadIdx.x; i < (1 << kHubLdsLg); i += blockDim.x) {
-    sk[i] = 0;
-    sv[i] = 0;
-  }
-  if (threadIdx.x == 0) s_claimed = 0;
-  __syncthreads();
-  constexpr uint32_t mask = (1u << kHubLdsLg) - 1;
-  for (int64_t e = row.lo + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < row.hi;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    int64_t w;
-    const int64_t x = g.nbr(row, e, w);
-    if (w == 0) continue;
-    const uint32_t lab = g.lab_at(comm, e, x), key = lab + 1;
-    uint32_t h = fib_hash(lab, 32 - kHubLdsLg);
-    bool done = false;
-    // at most kHubLdsKeys slots are ever claimed, so an empty slot is always reached
-    for (;;) {
-      const uint32_t k = sk[h];
-      if (k == key) {
-        atomicAdd(reinterpret_cast<unsigned long long *>(&sv[h]), (unsigned long long)w);
-        done = true;
-        break;
-      }
-      if (k == 0) {
-        if (atomicAdd(&s_claimed, 1) >= kHubLdsKeys) break;   // LDS table closed to new keys
-        const uint32_t prev = atomicCAS(&sk[h], 0u, key);
-        if (prev == 0 || prev == key) {
+  const WinRange win(L, kFamHub, r);
+  for (int y = blockIdx.y; y < win.n; y += gridDim.y) {
+    const int64_t v = g.unit_at(units, L.items[win.i0 + y].pos);
+    if (sd.frozen && sd.frozen[g.solve_of(v)]) continue;   // its solve is out of this sweep
+    GTab tab{gk + goff[v], gv + goff[v], glg[v]};
+    typename V::Row row = g.row(v, sd);
+    for (int i = threadIdx.x; i < (1 << kHubLdsLg); i += blockDim.x) {
+      sk[i] = 0;
+      sv[i] = 0;
+    }
+    if (threadIdx.x == 0) s_claimed = 0;
+    __syncthreads();
+    constexpr uint32_t mask = (1u << kHubLdsLg) - 1;
+    for (int64_t e = row.lo + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < row.hi;
+         e += (int64_t)gridDim.x * blockDim.x) {
+      int64_t w;
+      const int64_t x = g.nbr(row, e, w);
+      if (w == 0) continue;
+      const uint32_t lab = g.lab_at(comm, e, x), key = lab + 1;
+      uint32_t h = fib_hash(lab, 32 - kHubLdsLg);
+      bool done = false;
+      // at most kHubLdsKeys slots are ever claimed, so an empty slot is always reached
+      for (;;) {
+        const uint32_t k = sk[h];
+        if (k == key) {
           atomicAdd(reinterpret_cast<unsigned long long *>(&sv[h]), (unsigned long long)w);
           done = true;
           break;
         }
+        if (k == 0) {
+          if (atomicAdd(&s_claimed, 1) >= kHubLdsKeys) break;   // LDS table closed to new keys
+          const uint32_t prev = atomicCAS(&sk[h], 0u, key);
+          if (prev == 0 || prev == key) {
+            atomicAdd(reinterpret_cast<unsigned long long *>(&sv[h]), (unsigned long long)w);
+            done = true;
+            break;
+          }
+        }
+        h = (h + 1) & mask;
       }
-      h = (h + 1) & mask;
+      if (!done) tab.add(lab, w);
     }
-    if (!done) tab.add(lab, w);
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < (1 << kHubLdsLg); i += blockDim.x)
-    if (sk[i] != 0) tab.add(sk[i] - 1, sv[i]);
-  if (pc.c && blockIdx.x == 0 && threadIdx.x == 0) {
-    atomicAdd(pc.c + 0, 1ull);
-    atomicAdd(pc.c + 1, (unsigned long long)(row.hi - row.lo));
+    __syncthreads();
+    for (int i = threadIdx.x; i < (1 << kHubLdsLg); i += blockDim.x)
+      if (sk[i] != 0) tab.add(sk[i] - 1, sv[i]);
+    if (pc.c && blockIdx.x == 0 && threadIdx.x == 0) {
+      atomicAdd(pc.c + 0, 1ull);
+      atomicAdd(pc.c + 1, (unsigned long long)(row.hi - row.lo));
+    }
+    __syncthreads();   // the tables are reused for the next hub
   }
 }
 
 constexpr int kHubWin = 2048;   // table slots compacted at a time by a hub evaluation block
 
 template <class P, class V>
-__global__ __launch_bounds__(256) void k_hub_eval(V g, SolveDev sd, const int32_t *units,
-                                                  const uint32_t *comm, SliceTable sig,
-                                                  const int64_t *goff, const int32_t *glg,
-                                                  const uint32_t *gk, const int64_t *gv,
-                                                  typename P::Score *part, LmCounters pc) {
+__global__ __launch_bounds__(256) void k_hub_eval(V g, SolveDev sd, WinLevel L, int r,
+                                                  const int32_t *units, const uint32_t *comm,
+                                                  SliceTable sig, const int64_t *goff,
+                                                  const int32_t *glg, const uint32_t *gk,
+                                                  const int64_t *gv, typename P::Score *part,
+                                                  LmCounters pc) {
   __shared__ typename P::Score red[4];
-  const int64_t v = units[blockIdx.y];
-  const uint32_t D = comm[v];
-  const uint32_t *K = gk + goff[v];
-  const int64_t *Wt = gv + goff[v];
-  const int64_t size = 1ll << glg[v];
-  const int64_t span = (size + gridDim.x - 1) / gridDim.x;
-  const int64_t s0 = (int64_t)blockIdx.x * span, s1 = s0 + span < size ? s0 + span : size;
-  const UnitCtx u = unit_ctx(g, sd, v, D);
-  typename P::Score best = P::make(g, u, sd, sig, kNone, 0, kEmpty);
-  int ncand = 0;
-  bool coop = false;
-  if constexpr (!V::kLevel0 && IsMulti<P>::value) coop = u.m >= kCoopMinM;
-  if (coop) {
-    if constexpr (!V::kLevel0 && IsMulti<P>::value) {
-      // the block's span of the table is mostly empty slots: each window of kHubWin slots is
-      // first compacted into an LDS list of its candidates, and only those take coop turns
-      __shared__ int32_t wl[kHubWin];
-      __shared__ int wn;
-      const CoopLane c = coop_lane(g, u, sd, sig, threadIdx.x);
-      const int sub = threadIdx.x / c.mp, nsub = blockDim.x / c.mp;
-      for (int64_t w0 = s0; w0 < s1; w0 += kHubWin) {
-        const int64_t w1 = w0 + kHubWin < s1 ? w0 + kHubWin : s1;
-        if (threadIdx.x == 0) wn = 0;
-        __syncthreads();
-        for (int64_t i = w0 + threadIdx.x; i < w1; i += blockDim.x) {
-          const uint32_t key = K[i];
-          if (key != 0 && key - 1 != D) wl[atomicAdd(&wn, 1)] = (int32_t)(i - w0);
-        }
-        __syncthreads();
-        const int nw = wn;
-        for (int i0 = 0; i0 < nw; i0 += nsub * kCoopBatch) {
-          uint32_t lab[kCoopBatch];
-          int64_t W[kCoopBatch], y[kCoopBatch];
-          bool ok[kCoopBatch];
-          for (int k = 0; k < kCoopBatch; k++) {
-            const int ii = i0 + k * nsub + sub;
-            const int64_t i = ii < nw ? w0 + wl[ii] : -1;
-            const uint32_t key = i >= 0 ? K[i] : 0u;
-            lab[k] = key - 1;
-            ok[k] = key != 0;
-            W[k] = ok[k] ? Wt[i] : 0;
-            ok[k] = ok[k] && !P::prunable(u, W[k], best);
+  __shared__ int32_t wl[kHubWin];
+  __shared__ int wn;
+  const WinRange win(L, kFamHub, r);
+  const int32_t hub0 = L.ip[kFamHub * (L.ncol + 1)];
+  if (sd.redo) sd.redo = L.near_tie + r * L.J;
+  for (int y = blockIdx.y; y < win.n; y += gridDim.y) {
+    const WinItem it = L.items[win.i0 + y];
+    const int64_t v = g.unit_at(units, it.pos);
+    if (sd.frozen && sd.frozen[g.solve_of(v)]) continue;
+    sd.mark = it.colour;
+    const uint32_t D = comm[v];
+    const uint32_t *K = gk + goff[v];
+    const int64_t *Wt = gv + goff[v];
+    const int64_t size = 1ll << glg[v];
+    const int64_t span = (size + gridDim.x - 1) / gridDim.x;
+    const int64_t s0 = (int64_t)blockIdx.x * span, s1 = s0 + span < size ? s0 + span : size;
+    const UnitCtx u = unit_ctx(g, sd, v, D);
+    typename P::Score best = P::make(g, u, sd, sig, kNone, 0, kEmpty);
+    int ncand = 0;
+    bool coop = false;
+    if constexpr (!V::kLevel0 && IsMulti<P>::value) coop = u.m >= kCoopMinM;
+    if (coop) {
+      if constexpr (!V::kLevel0 && IsMulti<P>::value) {
+        // the block's span of the table is mostly empty slots: each window of kHubWin slots is
+        // first compacted into an LDS list of its candidates, and only those take coop turns
+        const CoopLane c = coop_lane(g, u, sd, sig, threadIdx.x);
+        const int sub = threadIdx.x / c.mp, nsub = blockDim.x / c.mp;
+        for (int64_t w0 = s0; w0 < s1; w0 += kHubWin) {
+          const int64_t w1 = w0 + kHubWin < s1 ? w0 + kHubWin : s1;
+          if (threadIdx.x == 0) wn = 0;
+          __syncthreads();
+          for (int64_t i = w0 + threadIdx.x; i < w1; i += blockDim.x) {
+            const uint32_t key = K[i];
+            if (key != 0 && key - 1 != D) wl[atomicAdd(&wn, 1)] = (int32_t)(i - w0);
           }
-          coop_lookup<kCoopBatch>(c, lab, ok, y);
-          for (int k = 0; k < kCoopBatch; k++) {
-            if (!ok[k]) continue;
-            ncand += c.j == 0;
-            ScoreK sc = coop_score(u, c, lab[k], W[k], y[k], kTarget);
-            if (better<P>(g, u, sd, sig, sc, best)) best = sc;
+          __syncthreads();
+          const int nw = wn;
+          for (int i0 = 0; i0 < nw; i0 += nsub * kCoopBatch) {
+            uint32_t lab[kCoopBatch];
+            int64_t W[kCoopBatch], y2[kCoopBatch];
+            bool ok[kCoopBatch];
+            for (int k = 0; k < kCoopBatch; k++) {
+              const int ii = i0 + k * nsub + sub;
+              const int64_t i = ii < nw ? w0 + wl[ii] : -1;
+              const uint32_t key = i >= 0 ? K[i] : 0u;
+              lab[k] = key - 1;
+              ok[k] = key != 0;
+              W[k] = ok[k] ? Wt[i] : 0;
+              ok[k] = ok[k] && !P::prunable(u, W[k], best);
+            }
+            coop_lookup<kCoopBatch>(c, lab, ok, y2);
+            for (int k = 0; k < kCoopBatch; k++) {
+              if (!ok[k]) continue;
+              ncand += c.j == 0;
+              ScoreK sc = coop_score(u, c, lab[k], W[k], y2[k], kTarget);
+              if (better<P>(g, u, sd, sig, sc, best)) best = sc;
+            }
           }
+          __syncthreads();   // the list is rewritten by the next window
         }
-        __syncthreads();   // the list is rewritten by the next window
+      }
+    } else {
+      for (int64_t i = s0 + threadIdx.x; i < s1; i += blockDim.x) {
+        const uint32_t key = K[i];
+        if (key == 0 || key - 1 == D) continue;
+        const int64_t W = Wt[i];
+        if (P::prunable(u, W, best)) continue;
+        ncand++;
+        typename P::Score sc = P::make(g, u, sd, sig, key - 1, W, kTarget);
+        if (better<P>(g, u, sd, sig, sc, best)) best = sc;
       }
     }
-  } else {
-    for (int64_t i = s0 + threadIdx.x; i < s1; i += blockDim.x) {
-      const uint32_t key = K[i];
-      if (key == 0 || key - 1 == D) continue;
-      const int64_t W = Wt[i];
-      if (P::prunable(u, W, best)) continue;
-      ncand++;
-      typename P::Score sc = P::make(g, u, sd, sig, key - 1, W, kTarget);
-      if (better<P>(g, u, sd, sig, sc, best)) best = sc;
-    }
+    if (pc.c && ncand) atomicAdd(pc.c + 2, (unsigned long long)ncand);
+    best = group_best<P>(BlockGrp(), g, u, sd, sig, best, red);
+    if (threadIdx.x == 0) part[(int64_t)(win.i0 + y - hub0) * gridDim.x + blockIdx.x] = best;
   }
-  if (pc.c && ncand) atomicAdd(pc.c + 2, (unsigned long long)ncand);
-  best = group_best<P>(BlockGrp(), g, u, sd, sig, best, red);
-  if (threadIdx.x == 0) part[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = best;
 }
 
 template <class P, class V>
-__global__ __launch_bounds__(64) void k_hub_final(V g, SolveDev sd, const int32_t *units,
-                                                  int64_t count, const uint32_t *comm,
+__global__ __launch_bounds__(64) void k_hub_final(V g, SolveDev sd, WinLevel L, int r,
+                                                  const int32_t *units, const uint32_t *comm,
                                                   SliceTable sig, const int64_t *goff,
                                                   const int32_t *glg, const uint32_t *gk,
                                                   const int64_t *gv,
                                                   const typename P::Score *part, int nparts,
                                                   uint32_t *target, uint32_t fresh_base) {
-  const int64_t idx = blockIdx.x;
-  if (idx >= count) return;
+  const WinRange win(L, kFamHub, r);
+  const int32_t hub0 = L.ip[kFamHub * (L.ncol + 1)];
+  if (sd.redo) sd.redo = L.near_tie + r * L.J;
   const int lane = threadIdx.x & 63;
-  const int64_t v = units[idx];
-  const uint32_t D = comm[v];
-  const UnitCtx u = unit_ctx(g, sd, v, D);
-  typename P::Score best = P::make(g, u, sd, sig, kNone, 0, kEmpty);
-  if (lane < nparts) best = part[idx * nparts + lane];
-  best = wave_best<P>(g, u, sd, sig, best);
-  GTab tab{const_cast<uint32_t *>(gk) + goff[v], const_cast<int64_t *>(gv) + goff[v], glg[v]};
-  const int64_t wD = tab.get(D);
-  typename P::Score stay;
-  bool coop = false;
-  if constexpr (!V::kLevel0 && IsMulti<P>::value) coop = u.m >= kCoopMinM;
-  if (coop) {
-    if constexpr (!V::kLevel0 && IsMulti<P>::value)
-      stay = coop_make(u, coop_lane(g, u, sd, sig, lane), D, wD, kStay);
-  } else {
-    stay = P::make(g, u, sd, sig, D, wD, kStay);
-  }
-  if (lane == 0) {
-    uint32_t out = kNone;
-    if (P::cmp(g, u, sd, sig, best, stay) > 0)
-      out = best.lab == kNone ? fresh_of(sd, fresh_base) + (uint32_t)g.orig(v) : best.lab;
-    target[idx] = out;
+  for (int y = blockIdx.x; y < win.n; y += gridDim.x) {
+    const WinItem it = L.items[win.i0 + y];
+    const int64_t v = g.unit_at(units, it.pos);
+    if (sd.frozen && sd.frozen[g.solve_of(v)]) {
+      if (lane == 0) target[it.pos] = kNone;
+      continue;
+    }
+    sd.mark = it.colour;
+    const uint32_t D = comm[v];
+    const UnitCtx u = unit_ctx(g, sd, v, D);
+    typename P::Score best = P::make(g, u, sd, sig, kNone, 0, kEmpty);
+    if (lane < nparts) best = part[(int64_t)(win.i0 + y - hub0) * nparts + lane];
+    best = wave_best<P>(g, u, sd, sig, best);
+    GTab tab{const_cast<uint32_t *>(gk) + goff[v], const_cast<int64_t *>(gv) + goff[v], glg[v]};
+    const int64_t wD = tab.get(D);
+    typename P::Score stay;
+    bool coop = false;
+    if constexpr (!V::kLevel0 && IsMulti<P>::value) coop = u.m >= kCoopMinM;
+    if (coop) {
+      if constexpr (!V::kLevel0 && IsMulti<P>::value)
+        stay = coop_make(u, coop_lane(g, u, sd, sig, lane), D, wD, kStay);
+    } else {
+      stay = P::make(g, u, sd, sig, D, wD, kStay);
+    }
+    if (lane == 0) {
+      uint32_t out = kNone;
+      if (P::cmp(g, u, sd, sig, best, stay) > 0)
+        out = best.lab == kNone ? fresh_of(sd, fresh_base) + (uint32_t)g.orig(v) : best.lab;
+      Emit{target, L.first_move + r, it.colour}.put(it.pos, out);
+    }
   }
 }
 
-// Apply the decided moves of one colour batch: new label, Sigma delta for every profile slice.
+// Apply the moves of pair r's window (those of its first moving colour): new label, Sigma delta
+// for every profile slice, the label copy of level 0; and set up the next window.  Few units
+// take a wave each, its lanes over the profile slices (up to 64, two Sigma atomics each) or the
+// row; many units take a thread each, the long rows of the movers a wave.  Near-ties of the
+// colours whose decisions count ask for a repeat of their solve's sweep.
 template <class V>
-__global__ __launch_bounds__(256) void k_lm_apply(V g, const int32_t *units, int64_t count,
-                                                  const uint32_t *target, uint32_t *comm,
-                                                  SliceTable sig, uint32_t *moved,
-                                                  const uint8_t *frozen) {
+__global__ __launch_bounds__(256) void k_win_apply(V g, WinLevel L, int r,
+                                                   const int32_t *units, const uint32_t *target,
+                                                   uint32_t *comm, SliceTable sig,
+                                                   uint32_t *moved, int32_t *redo) {
   __shared__ uint32_t s_moves;
-  __shared__ int s_j, s_mixed;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  bool mv = false;
-  int j = 0;
-  if (threadIdx.x == 0) {
-    s_moves = 0;
-    s_mixed = 0;
-    s_j = g.solve_of(units[i]);   // thread 0's unit always exists
+  const WinState s = L.st[r];
+  const int f = L.first_move[r];
+  const bool live = s.c0 < s.c1, dirty = live && f < s.c1;
+  if (blockIdx.x == 0) {
+    if (threadIdx.x < 64) {
+      const int next = (r + 1) % 3;
+      const int c0 = !live ? s.c0 : dirty ? f + 1 : s.c1;
+      int budget = s.budget;
+      const int t = s.t;
+      if (dirty && L.moved_at[f] < t - 1) {   // an unforeseen move: look less far ahead
+        const int used = L.cost[c0] - L.cost[s.c0];
+        budget = used > L.floor ? used : L.floor;
+      } else if (live && !dirty && budget < kWinUnbounded) {
+        budget *= 4;
+      }
+      const int c1 = win_end(L, t, c0, budget);
+      if (threadIdx.x == 0) {
+        if (dirty) L.moved_at[f] = t;
+        L.st[next] = WinState{c0, c1, budget, s.windows + (live ? 1 : 0), t};
+        L.first_move[(r + 2) % 3] = kNoColour;
+      }
+    }
+    if (L.near_tie)
+      for (int j = threadIdx.x; j < L.J; j += blockDim.x) {
+        const int c = L.near_tie[r * L.J + j];
+        if (live && c < s.c1 && c <= f) redo[j] = 0;
+        L.near_tie[((r + 2) % 3) * L.J + j] = kNoColour;
+      }
   }
+  if (!dirty) return;
+  const int lo = L.cptr[f], hi = L.cptr[f + 1];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int waves = gridDim.x * 4;
+  if (hi - lo <= 2 * waves) {
+    for (int i = lo + blockIdx.x * 4 + wv; i < hi; i += waves) {
+      const uint32_t C = target[i];
+      if (C == kNone) continue;
+      const int64_t v = g.unit_at(units, i);
+      const uint32_t D = comm[v];
+      const int m = g.plen(v);
+      for (int jj = lane; jj < m; jj += 64) {
+        int gs;
+        int64_t k;
+        g.pent(v, jj, gs, k);
+        tab_add(sig, gs, D, -(int32_t)k);
+        tab_add(sig, gs, C, (int32_t)k);
+      }
+      if constexpr (std::is_same<V, ViewP>::value) {
+        if (g.elab)   // the entries pointing at v see its new label
+          for (int64_t e = g.rp[v] + lane; e < g.rp[v + 1]; e += 64) g.elab[g.prev[e]] = C;
+      }
+      if (lane == 0) {
+        comm[v] = C;
+        atomicAdd(moved + g.solve_of(v), 1u);
+      }
+    }
+    return;
+  }
+  if (threadIdx.x == 0) s_moves = 0;
   __syncthreads();
-  if (i < count) {
-    const uint32_t C = target[i];
-    const int64_t v = units[i];
-    j = g.solve_of(v);
-    if (C != kNone && !frozen[j]) {
+  uint32_t mine = 0;
+  for (int i0 = lo + (blockIdx.x * 4 + wv) * 64; i0 < hi; i0 += waves * 64) {
+    const int i = i0 + lane;
+    const uint32_t C = i < hi ? target[i] : kNone;
+    const bool mv = C != kNone;
+    int64_t v = 0;
+    int j = 0;
+    if (mv) {
+      v = g.unit_at(units, i);
+      j = g.solve_of(v);
       const uint32_t D = comm[v];
       const int m = g.plen(v);
       for (int jj = 0; jj < m; jj++) {
@@ -1872,54 +1887,32 @@ __global__ __launch_bounds__(256) void k_lm_apply(V g, const int32_t *units, int
         tab_add(sig, gs, C, (int32_t)k);
       }
       comm[v] = C;
-      if constexpr (std::is_same<V, ViewP>::value) {
-        if (g.elab)   // the entries pointing at v see its new label
-          for (int64_t e = g.rp[v]; e < g.rp[v + 1]; e++) g.elab[g.prev[e]] = C;
-      }
-      mv = true;
+      mine++;
     }
-    if (j != s_j) s_mixed = 1;
-    if (mv) atomicAdd(&s_moves, 1u);
+    if (L.J > 1) wave_count(moved, j, mv);
+    if constexpr (std::is_same<V, ViewP>::value) {
+      if (g.elab) {
+        int64_t e0 = 0, e1 = 0;
+        if (mv) {
+          e0 = g.rp[v];
+          e1 = g.rp[v + 1];
+        }
+        const bool wide = e1 - e0 > 16;
+        if (!wide)
+          for (int64_t e = e0; e < e1; e++) g.elab[g.prev[e]] = C;
+        for (uint64_t b = __ballot(wide); b; b &= b - 1) {
+          const int l = __builtin_ctzll(b);
+          const int64_t a0 = __shfl(e0, l, 64), a1 = __shfl(e1, l, 64);
+          const uint32_t c = (uint32_t)__shfl((int)C, l, 64);
+          for (int64_t e = a0 + lane; e < a1; e += 64) g.elab[g.prev[e]] = c;
+        }
+      }
+    }
   }
-  __syncthreads();
-  // one atomic per block when all its units belong to one solve (the usual case)
-  if (!s_mixed) {
-    if (threadIdx.x == 0 && s_moves) atomicAdd(moved + s_j, s_moves);
-  } else {
-    wave_count(moved, j, mv);
-  }
-}
-
-// The moves of a small batch, one wave per unit with the lanes over its profile slices (a
-// unit of an aggregated level spans up to 64 slices, two Sigma atomics each).
-template <class V>
-__global__ __launch_bounds__(256) void k_lm_apply_wave(V g, const int32_t *units, int64_t count,
-                                                       const uint32_t *target, uint32_t *comm,
-                                                       SliceTable sig, uint32_t *moved,
-                                                       const uint8_t *frozen) {
-  const int lane = threadIdx.x & 63;
-  const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (i >= count) return;
-  const uint32_t C = target[i];
-  const int64_t v = units[i];
-  const int j = g.solve_of(v);
-  if (C == kNone || frozen[j]) return;
-  const uint32_t D = comm[v];
-  const int m = g.plen(v);
-  for (int jj = lane; jj < m; jj += 64) {
-    int gs;
-    int64_t k;
-    g.pent(v, jj, gs, k);
-    tab_add(sig, gs, D, -(int32_t)k);
-    tab_add(sig, gs, C, (int32_t)k);
-  }
-  if constexpr (std::is_same<V, ViewP>::value) {
-    if (g.elab)
-      for (int64_t e = g.rp[v] + lane; e < g.rp[v + 1]; e += 64) g.elab[g.prev[e]] = C;
-  }
-  if (lane == 0) {
-    comm[v] = C;
-    atomicAdd(moved + j, 1u);
+  if (L.J == 1) {
+    if (mine) atomicAdd(&s_moves, mine);
+    __syncthreads();
+    if (threadIdx.x == 0 && s_moves) atomicAdd(moved, s_moves);
   }
 }
 
@@ -1945,10 +1938,10 @@ __global__ void k_profile_slice_count(const int32_t *ps, int64_t ne, int nslices
 
 // Labels of the units of flagged solves back to their copy from the start of the sweep.
 template <class V>
-__global__ void k_restore_flagged(V g, int64_t n, const uint32_t *snap, const uint32_t *redo,
+__global__ void k_restore_flagged(V g, int64_t n, const uint32_t *snap, const int32_t *redo,
                                   uint32_t *comm) {
   const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (v < n && redo[g.usolve[v]]) comm[v] = snap[v];
+  if (v < n && redo[g.usolve[v]] != kRedoUnset) comm[v] = snap[v];
 }
 
 // ------------------------------------------------------------------ level 0 by position
@@ -1968,8 +1961,8 @@ __global__ void k_pos_label_keys(const uint32_t *keys, const int32_t *units,
 
 // per position: degree (for the row starts), intra degree, slice, solve, labels
 __global__ void k_pos_meta(View0 g, const int32_t *units, int64_t n, int64_t *deg, int32_t *pk,
-                           int32_t *pslice, int32_t *psolve, int32_t *iota,
-                           const uint32_t *comm, uint32_t *pcomm) {
+                           int32_t *pslice, int32_t *psolve, const uint32_t *comm,
+                           uint32_t *pcomm) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i > n) return;
   if (i == n) {
@@ -1984,7 +1977,6 @@ __global__ void k_pos_meta(View0 g, const int32_t *units, int64_t n, int64_t *de
   pk[i] = (int32_t)kk;
   pslice[i] = gs;
   if (psolve) psolve[i] = g.solve_of(v);
-  iota[i] = (int32_t)i;
   pcomm[i] = comm[v];
 }
 
@@ -2069,12 +2061,12 @@ __global__ void k_pos_elab_refresh(const int32_t *pcol, int64_t nnz, const uint3
 // solves' units are set aside (inactive, so the proposal kernels skip them) and get their
 // flags back afterwards (k_ref_redo_done), keeping their proposals of the first pass.
 template <class V>
-__global__ void k_ref_redo_prep(V g, int64_t n, const uint32_t *redo, uint8_t *active,
+__global__ void k_ref_redo_prep(V g, int64_t n, const int32_t *redo, uint8_t *active,
                                 const uint8_t *snap_a, uint32_t *propr, const uint32_t *snap_p,
                                 uint8_t *keep) {
   const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (v >= n) return;
-  if (redo[g.solve_of(v)]) {
+  if (redo[g.solve_of(v)] != kRedoUnset) {
     active[v] = snap_a[v];
     propr[v] = snap_p[v];
   } else {
@@ -2083,10 +2075,10 @@ __global__ void k_ref_redo_prep(V g, int64_t n, const uint32_t *redo, uint8_t *a
   }
 }
 template <class V>
-__global__ void k_ref_redo_done(V g, int64_t n, const uint32_t *redo, uint8_t *active,
+__global__ void k_ref_redo_done(V g, int64_t n, const int32_t *redo, uint8_t *active,
                                 const uint8_t *keep) {
   const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (v < n && !redo[g.solve_of(v)]) active[v] = keep[v];
+  if (v < n && redo[g.solve_of(v)] == kRedoUnset) active[v] = keep[v];
 }
 
 template <class V>

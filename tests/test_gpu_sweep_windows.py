@@ -1,0 +1,76 @@
+"""GPU: sweeps decide windows of several colours at once; memberships, Q components and the
+schedule's statistics must equal the oracle's where a window can go wrong: more colours than a
+wave has lanes, hub units (above the block table's 4096 entries) between ordinary ones, windows
+as narrow and as wide as the tuning allows, one kernel for both unit classes or one each, and
+unions of solves that stop at different sweeps."""
+from fractions import Fraction as F
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2608_03695_amd import gen
+
+pytestmark = pytest.mark.gpu
+
+STAT_KEYS = ["sweeps", "moves", "sweep_cap_hits", "refine_rounds", "merges", "splits",
+             "levels_run", "iterations_run", "n_communities"]
+
+
+def _dense():
+    """More than 64 colours at level 0 and above (each snapshot holds cliques of 70 nodes)."""
+    rng = np.random.default_rng(3)
+    slices = []
+    for _ in range(24):
+        perm = rng.permutation(420)
+        edges = [(int(perm[c * 70 + i]), int(perm[c * 70 + j])) for c in range(6)
+                 for i in range(70) for j in range(i)]
+        edges += [(int(a), int(b)) for a, b in rng.integers(0, 420, (2000, 2)) if a != b]
+        slices.append(edges)
+    return gen.from_edge_lists(420, slices, name="cliques")
+
+
+def _hubs():
+    """Two nodes joined to most others, in a graph of small communities."""
+    base = gen.dcsbm(6000, 2, 6, 60, 0.2, 2.5, 0.05, seed=5)
+    rng = np.random.default_rng(4)
+    slices = []
+    for s in range(2):
+        u, x, _ = base.slice_edges(s)
+        edges = [(int(a), int(b)) for a, b in zip(u, x)]
+        for hub in (0, 1):
+            edges += [(hub, int(b)) for b in rng.choice(np.arange(2, 6000), 5200, replace=False)]
+        slices.append(edges)
+    return gen.from_edge_lists(6000, slices, name="hubs")
+
+
+GRAPHS = [("dense", _dense, F(1), F(1, 2)), ("hubs", _hubs, F(2), F(1))]
+TUNINGS = [dict(), dict(lat_parts_max=1), dict(latency_units=64, split_group_units=0),
+           dict(latency_units=65536, split_group_units=1 << 30, lat_parts_max=2)]
+
+
+@pytest.mark.parametrize("name,make,gamma,omega", GRAPHS, ids=[g[0] for g in GRAPHS])
+def test_windows_match_oracle(name, make, gamma, omega):
+    from paper_2608_03695_amd import mslm
+    tg = make()
+    om, oc, ost = oracle.OracleGraph(tg, omega).leiden(gamma, max_levels=32, max_iterations=2,
+                                                       seed=0)
+    g = mslm.Graph(tg, omega)
+    default = g.tuning()
+    for tu in TUNINGS:
+        g.set_tuning(**default)
+        g.set_tuning(**tu)
+        m, r = g.leiden(gamma)
+        assert np.array_equal(m, om), tu
+        assert np.array_equal(r["q_components"], oc), tu
+        for k in STAT_KEYS:
+            assert r[k] == ost[k], (tu, k)
+    g.set_tuning(**default)
+    solves = [(0, gamma, omega, 32, 2, 0), (0, F(1, 2), F(10), 32, 1, 1), (0, gamma, omega, 2, 2, 0)]
+    for sv, (m, r) in zip(solves, mslm.batch_leiden([g], solves)):
+        pm, pr = g.leiden(sv[1], sv[2], max_levels=sv[3], max_iterations=sv[4], seed=sv[5])
+        assert np.array_equal(m, pm), sv
+        assert np.array_equal(r["q_components"], pr["q_components"]), sv
+        for k in STAT_KEYS:
+            assert r[k] == pr[k], (sv, k)
+    g.close()
