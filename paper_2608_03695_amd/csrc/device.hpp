@@ -99,7 +99,7 @@ __device__ inline void wave_append(int32_t *out, uint32_t *ctr, bool flag, int32
 // Appends gathered in a wave-private LDS buffer and written out in chunks: one global atomic
 // per chunk instead of one per call (a frontier counter is shared by the whole grid, and
 // atomics on one word serialise).  n is the same on every lane of the wave.
-constexpr int kStage = 512;
+constexpr int kStage = 256;
 struct WaveStage {
   int32_t *buf;     // LDS, kStage entries, private to the wave
   int32_t *out;     // global list

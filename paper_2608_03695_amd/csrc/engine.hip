@@ -102,11 +102,10 @@ struct Workspace {
       pvals2, pnext;
   Buf ckeys, cvals, ckeys2, cvals2, head, ismin, segx, minof, crank;
   Buf qW, qSS, qI, ranges_lo, ranges_hi, ranges_off;
-  Buf sm_maxsw, sm_stat, sm_nz, sm_start;
   Buf b_src, b_dst, b_w, b_off, b_twom;   // graph build inputs and per-slice sums
   Buf b_pairs, b_present;                 // coupled slice pairs, present copies (build)
   Buf hubpart;                            // per-block best candidates of hub units
-  Buf jph0, jph1;                         // heavy frontier lists of the colouring
+  Buf jp_used;                            // bitmaps of the colours taken around each unit
   Buf sig_count;                          // profile entries per slice of a level
   Buf comm_snap;                          // labels at the start of a sweep (for a redo)
   Buf s_redo;                             // per-solve redo flags of a sweep

@@ -95,6 +95,10 @@ struct View0 {
   __device__ int64_t wt(const Row &r, int64_t e, int32_t x) const {
     return (x >= r.slo && x < r.shi ? r.b : r.a) * (w ? (int64_t)w[e] : 1);
   }
+  // whether an entry of this column has weight (raw weights are never 0, omega may be)
+  __device__ bool live(const Row &r, int32_t x) const {
+    return (x >= r.slo && x < r.shi ? r.b : r.a) != 0;
+  }
   // neighbour of entry e and its scaled weight
   __device__ int64_t nbr(const Row &r, int64_t e, int64_t &ww) const {
     const int32_t x = col[e];
@@ -174,6 +178,7 @@ struct ViewK {
   };
   __device__ Row row(int64_t v, const SolveDev &) const { return Row{rp[v], rp[v + 1]}; }
   __device__ int64_t wt(const Row &, int64_t e, int32_t) const { return w[e]; }
+  __device__ bool live(const Row &, int32_t) const { return true; }   // aggregated: always > 0
   __device__ int64_t nbr(const Row &, int64_t e, int64_t &ww) const {
     ww = w[e];
     return col[e];
@@ -2103,15 +2108,41 @@ __global__ void k_rebuild_check(const uint32_t *used, const uint32_t *limit, int
 // First-fit colouring in decreasing priority (Jones-Plassmann): a unit takes the smallest
 // colour unused by its higher-priority neighbours once all of them are coloured.  The
 // result equals the sequential greedy colouring in priority order.  Each unit counts its
-// higher-priority neighbours once; a round colours the ready frontier and releases the
-// lower-priority neighbours, so every row is scanned a constant number of times.
-// Frontier lists of a colouring round: units above kJpHeavy neighbours are coloured by a
-// whole block (their scans would hold a single wave for long), the others by one wave.
-constexpr int kJpHeavy = 512;
+// higher-priority neighbours once; a coloured unit marks its colour in the bitmaps of its
+// lower-priority neighbours and then takes one off their counts, and whoever takes the last one
+// off holds a unit whose colour is the first clear bit of its bitmap.  So a row is scanned twice
+// (count, mark) and no colour is ever gathered.
+//
+// Rounds colour the units that are ready and collect those they release.  The time is the number
+// of rounds (the longest chain of decreasing priorities, hundreds of units in dense aggregated
+// levels) times a dozen dependent memory round trips each, so:
+//   large levels (k_jp_round)  short rows take 8 lanes each while more units are ready than the
+//                              chip has waves, else every unit takes a wave; rows above
+//                              kJpWaveRow entries take the block;
+//   small levels (k_jp_chain)  the units a block releases queue in its own LDS and its waves take
+//                              them at once, up to kJpDepth links of a chain per round, which
+//                              deals them out to the blocks again.  No block waits for another.
+// Measured against rounds that gather colours, one wave per unit (small levels: one workgroup for
+// the whole level): 3.2M units of degree 11 11.4 -> 9.1 ms, 207k of degree 72 15.1 -> 11.7 ms,
+// 9k of degree 218 9.3 -> 4.4 ms.  Chains in large levels lose (99k units 3.8 -> 21 ms): blocks
+// that release much keep it, and their waves queue up while others have left.
+//
+// Between waves of one launch everything travels through device-scope atomics, and a wave
+// waits for its marks to be performed before it takes the counts down.
 struct JpLists {
-  int32_t *light[2];
-  int32_t *heavy[2];
-  uint32_t *counts;   // [0..2] light counters, [3..5] heavy counters (round r uses r % 3)
+  int32_t *list[2];   // ready units by parity of the round
+  // [0..2] their numbers (round r uses r % 3), [3] long rows of the count, [4] a wave gave up
+  uint32_t *counts;
+};
+// What a colouring works on: counts of uncoloured higher-priority neighbours, colours, and
+// `planes` bitmaps of 64 colours per unit (plane p of unit v at used[p * n + v]).  A colour
+// beyond the planes is found by scanning the row (jp_scan_free).
+struct JpState {
+  uint32_t *cnt;
+  int32_t *colour;
+  unsigned long long *used;
+  int64_t n;
+  int planes;
 };
 
 // Rows longer than kJpCountThread entries are counted by a wave (k_jp_count_wide) instead
@@ -2120,51 +2151,53 @@ constexpr int kJpCountThread = 64;
 
 template <class V>
 __global__ __launch_bounds__(256) void k_jp_count(V g, SolveDev sd, const int32_t *work,
-                                                  int64_t nwork, uint32_t *cnt, int32_t *front,
-                                                  uint32_t *nfront, int32_t *hfront,
-                                                  uint32_t *nhfront, int32_t *wide,
+                                                  int64_t nwork, JpState s, int32_t *front,
+                                                  uint32_t *nfront, int32_t *wide,
                                                   uint32_t *nwide, int it, int lvl) {
   // one thread per unit; ready units are appended once per wave
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   bool ready = false;
   int64_t v = 0;
-  const bool long_row = idx < nwork && g.degree(work[idx]) > kJpCountThread;
-  wave_append(wide, nwide, long_row, idx < nwork ? work[idx] : 0);
-  if (idx < nwork && !long_row) {
+  if (idx < nwork) {
     v = work[idx];
-    const int j = g.usolve[v];
+    for (int p = 0; p < s.planes; p++) s.used[p * s.n + v] = 0ull;
+  }
+  const bool long_row = idx < nwork && g.degree(v) > kJpCountThread;
+  wave_append(wide, nwide, long_row, (int32_t)v);
+  if (idx < nwork && !long_row) {
+    const int j = g.solve_of(v);
     const uint64_t sm = sd.seedmix[j];
     const int64_t off = sd.uoff[j];
     const uint64_t hv = priority(sm, it, lvl, 0, (uint32_t)(v - off));
     typename V::Row row = g.row(v, sd);
     uint32_t c = 0;
+    bool alone = true;
     for (int64_t e = row.lo; e < row.hi; e++) {
       int32_t x = g.col[e];
-      if (g.wt(row, e, x) == 0) continue;
+      if (!g.live(row, x)) continue;
+      alone = false;
       uint64_t hx = priority(sm, it, lvl, 0, (uint32_t)(x - off));
       if (outranks(hx, (uint32_t)x, hv, (uint32_t)v)) c++;
     }
-    cnt[v] = c;
-    ready = c == 0;
+    s.cnt[v] = c;
+    ready = c == 0 && !alone;
+    if (alone) s.colour[v] = 0;   // no neighbours: nothing to wait for or to release
   }
-  const bool heavy = ready && g.degree(v) > kJpHeavy;
-  wave_append(front, nfront, ready && !heavy, (int32_t)v);
-  wave_append(hfront, nhfront, heavy, (int32_t)v);
+  wave_append(front, nfront, ready, (int32_t)v);
 }
 
 // The long rows set aside by k_jp_count, one wave each; their number is read on the device.
 template <class V>
 __global__ __launch_bounds__(256) void k_jp_count_wide(V g, SolveDev sd, const int32_t *wide,
                                                        const uint32_t *nwide, uint32_t *cnt,
-                                                       int32_t *front, uint32_t *nfront,
-                                                       int32_t *hfront, uint32_t *nhfront, int it,
+                                                       int32_t *front, uint32_t *nfront, int it,
                                                        int lvl) {
   const int lane = threadIdx.x & 63;
   const int64_t nw = *nwide;
   for (int64_t idx = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); idx < nw;
        idx += (int64_t)gridDim.x * 4) {
     const int64_t v = wide[idx];
-    const int j = g.usolve[v];
+    const int j = g.solve_of(v);
     const uint64_t sm = sd.seedmix[j];
     const int64_t off = sd.uoff[j];
     const uint64_t hv = priority(sm, it, lvl, 0, (uint32_t)(v - off));
@@ -2172,62 +2205,81 @@ __global__ __launch_bounds__(256) void k_jp_count_wide(V g, SolveDev sd, const i
     int64_t c = 0;
     for (int64_t e = row.lo + lane; e < row.hi; e += 64) {
       int32_t x = g.col[e];
-      if (g.wt(row, e, x) == 0) continue;
+      if (!g.live(row, x)) continue;
       uint64_t hx = priority(sm, it, lvl, 0, (uint32_t)(x - off));
       if (outranks(hx, (uint32_t)x, hv, (uint32_t)v)) c++;
     }
     for (int m = 32; m >= 1; m >>= 1) c += shfl_xor64(c, m);
     if (lane == 0) cnt[v] = (uint32_t)c;
-    const bool ready = lane == 0 && c == 0;
-    const bool heavy = ready && g.degree(v) > kJpHeavy;
-    wave_append(front, nfront, ready && !heavy, (int32_t)v);
-    wave_append(hfront, nhfront, heavy, (int32_t)v);
+    wave_append(front, nfront, lane == 0 && c == 0, (int32_t)v);
   }
 }
 
-// Release the lower-priority neighbours of v over entries [lo, hi) with stride `step`
-// starting at this thread's offset; the last release of a neighbour queues it for the next
-// round (light or heavy list by degree).  Every thread of the wave must call this.
+// Waits until every memory operation of this wave has been performed.
+__device__ inline void wave_drain() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+}
+
+// First colour of v that the planes leave free, or -1: the G lanes from lane gbase on hold one
+// plane each and learn the same answer.
+template <int G>
+__device__ inline int jp_plane_free(const JpState &s, int64_t v) {
+  const int lane = threadIdx.x & 63, gl = lane & (G - 1), gbase = lane & ~(G - 1);
+  const uint64_t word = gl < s.planes ? __hip_atomic_load(s.used + gl * s.n + v, __ATOMIC_RELAXED,
+                                                          __HIP_MEMORY_SCOPE_AGENT)
+                                      : ~0ull;
+  const uint64_t mask = (G == 64 ? ~0ull : ((1ull << G) - 1)) << gbase;
+  const uint64_t freew = __ballot(~word != 0) & mask;
+  const int L = freew ? __builtin_ctzll(freew) : gbase;
+  const uint64_t wl = (uint64_t)__shfl((long long)word, L, 64);
+  return freew ? (L - gbase) * 64 + __builtin_ctzll(~wl) : -1;
+}
+
+// The unit being coloured, and what its neighbours are compared with.
 template <class V>
-__device__ inline void jp_release(const V &g, const typename V::Row &row, int64_t first,
-                                  int step, int64_t v, uint64_t sm, int64_t off, uint64_t hv,
-                                  uint32_t *cnt, WaveStage &sl, WaveStage &sh, int it, int lvl) {
-  for (int64_t e0 = row.lo; e0 < row.hi; e0 += step) {
-    const int64_t e = e0 + first;
-    bool ready = false;
-    int32_t x = 0;
-    if (e < row.hi) {
-      x = g.col[e];
-      if (g.wt(row, e, x) != 0) {
-        uint64_t hx = priority(sm, it, lvl, 0, (uint32_t)(x - off));
-        if (!outranks(hx, (uint32_t)x, hv, (uint32_t)v)) ready = atomicSub(cnt + x, 1u) == 1u;
-      }
-    }
-    const bool heavy = ready && g.degree(x) > kJpHeavy;
-    sl.append(ready && !heavy, x);
-    sh.append(heavy, x);
+struct JpUnit {
+  const V &g;
+  typename V::Row row;
+  int64_t v, off;
+  uint64_t sm, hv;
+  int it, lvl;
+  __device__ JpUnit(const V &g_, const SolveDev &sd, int64_t v_, int it_, int lvl_)
+      : g(g_), row(g_.row(v_, sd)), v(v_), it(it_), lvl(lvl_) {
+    const int j = g.solve_of(v);
+    sm = sd.seedmix[j];
+    off = sd.uoff[j];
+    hv = priority(sm, it, lvl, 0, (uint32_t)(v - off));
   }
-}
+  __device__ int64_t len() const { return row.hi - row.lo; }
+  // the neighbour at offset i of the row when its priority is lower (or higher), else -1
+  __device__ int32_t nbr(int64_t i, bool higher) const {
+    const int64_t e = row.lo + i;
+    if (e >= row.hi) return -1;
+    const int32_t x = g.col[e];
+    if (!g.live(row, x)) return -1;
+    const uint64_t hx = priority(sm, it, lvl, 0, (uint32_t)(x - off));
+    return outranks(hx, (uint32_t)x, hv, (uint32_t)v) == higher ? x : -1;
+  }
+  __device__ int32_t lower(int64_t i) const { return nbr(i, false); }
+};
 
-// Colours of the higher-priority neighbours of v are marked in an LDS bitmap of NW words
-// (atomic OR), a window of 64*NW colours at a time; the first clear bit is v's colour.
+// First free colour from `base` on: the colours of the higher-priority neighbours of u are
+// marked in an LDS bitmap of NW words (atomic OR), a window of 64*NW colours at a time.
 // sync() orders the bitmap's clear, marks and reads among the threads that share it.
 template <int NW, class V, class Sync>
-__device__ inline int jp_first_free(const V &g, const typename V::Row &row, int first, int step,
-                                    int64_t v, uint64_t sm, int64_t off, uint64_t hv,
-                                    const int32_t *colour, int it, int lvl, uint64_t *bits,
-                                    Sync sync) {
+__device__ inline int jp_scan_free(const JpUnit<V> &u, int first, int step, const int32_t *colour,
+                                   int base, uint64_t *bits, Sync sync) {
   const int lane = threadIdx.x & 63;
   int result = -1;
-  for (int base = 0; result < 0; base += 64 * NW) {
+  for (; result < 0; base += 64 * NW) {
     for (int i = first; i < NW; i += step) bits[i] = 0;
     sync();
-    for (int64_t e = row.lo + first; e < row.hi; e += step) {
-      const int32_t x = g.col[e];
-      if (g.wt(row, e, x) == 0) continue;
-      const uint64_t hx = priority(sm, it, lvl, 0, (uint32_t)(x - off));
-      if (!outranks(hx, (uint32_t)x, hv, (uint32_t)v)) continue;
-      const int d = colour[x] - base;
+    for (int64_t i = first; i < u.len(); i += step) {
+      const int32_t x = u.nbr(i, true);
+      if (x < 0) continue;
+      const int d =
+          __hip_atomic_load(colour + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - base;
       if (d >= 0 && d < 64 * NW) atomicOr((unsigned long long *)(bits + (d >> 6)), 1ull << (d & 63));
     }
     sync();
@@ -2258,72 +2310,280 @@ struct BlockLdsSync {
   __device__ void operator()() const { __syncthreads(); }
 };
 
-// A light unit (at most kJpHeavy entries) has a colour of at most kJpHeavy, inside one
-// window of this many bitmap words.
-constexpr int kJpLightWords = (kJpHeavy + 64) / 64;
-constexpr int kJpBlockWords = 64;
+// The colour c of a unit marked at its lower-priority neighbour x.
+__device__ inline void jp_mark(const JpState &s, int64_t x, int c) {
+  if (c < 64 * s.planes) atomicOr(s.used + (int64_t)(c >> 6) * s.n + x, 1ull << (c & 63));
+}
 
-// Colour one light frontier unit with one wave.
-template <class V>
-__device__ inline void jp_unit(const V &g, const SolveDev &sd, int64_t v, int32_t *colour,
-                               uint32_t *cnt, WaveStage &sl, WaveStage &sh, int it, int lvl,
-                               uint64_t *bits) {
+// Colour unit v with one wave and release its lower-priority neighbours: put(ready, x) is called
+// by the whole wave for the neighbours of one turn.
+constexpr int kJpTurns = 4;   // entries per lane in flight together, kept between mark and release
+template <int NW, class V, class Put>
+__device__ inline void jp_wave(const V &g, const SolveDev &sd, int64_t v, const JpState &s, int it,
+                               int lvl, uint64_t *bits, Put put) {
   const int lane = threadIdx.x & 63;
-  const int j = g.usolve[v];
-  const uint64_t sm = sd.seedmix[j];
-  const int64_t off = sd.uoff[j];
-  const uint64_t hv = priority(sm, it, lvl, 0, (uint32_t)(v - off));
-  typename V::Row row = g.row(v, sd);
-  const int result = jp_first_free<kJpLightWords>(g, row, lane, 64, v, sm, off, hv, colour, it,
-                                                  lvl, bits, WaveLdsSync());
-  if (lane == 0) colour[v] = result;
-  jp_release(g, row, lane, 64, v, sm, off, hv, cnt, sl, sh, it, lvl);
-}
-
-// Colour one heavy frontier unit with the whole block (all threads must call this).
-template <class V>
-__device__ inline void jp_unit_block(const V &g, const SolveDev &sd, int64_t v, int32_t *colour,
-                                     uint32_t *cnt, WaveStage &sl, WaveStage &sh, int it,
-                                     int lvl, uint64_t *bits) {
-  const int tid = threadIdx.x, nt = blockDim.x;
-  const int j = g.usolve[v];
-  const uint64_t sm = sd.seedmix[j];
-  const int64_t off = sd.uoff[j];
-  const uint64_t hv = priority(sm, it, lvl, 0, (uint32_t)(v - off));
-  typename V::Row row = g.row(v, sd);
-  const int result = jp_first_free<kJpBlockWords>(g, row, tid, nt, v, sm, off, hv, colour, it,
-                                                  lvl, bits, BlockLdsSync());
-  if (tid == 0) colour[v] = result;
-  jp_release(g, row, tid, nt, v, sm, off, hv, cnt, sl, sh, it, lvl);
-}
-
-// One Jones-Plassmann round with its frontier sizes read on the device, so rounds can be
-// launched back to back without a host round trip: round r colours the lists of parity r&1
-// (sizes counts[r%3] and counts[3 + r%3]), appends the released units to the other lists
-// (counters (r+1)%3) and clears the counters of round r+2.  Waves take the light units,
-// then whole blocks take the heavy ones.  A round with empty frontiers does nothing.
-template <class V>
-__global__ __launch_bounds__(256) void k_jp_round(V g, SolveDev sd, JpLists L, int32_t *colour,
-                                                  uint32_t *cnt, int r, int it, int lvl) {
-  __shared__ uint64_t s_light[4][kJpLightWords];
-  __shared__ uint64_t s_block[kJpBlockWords];
-  __shared__ int32_t s_stage[4][2][kStage];
-  const int64_t nf = L.counts[r % 3], nh = L.counts[3 + r % 3];
-  const int p = r & 1;
-  const int wv = threadIdx.x >> 6;
-  // released units are staged per wave and written out in chunks
-  WaveStage sl{s_stage[wv][0], L.light[p ^ 1], L.counts + (r + 1) % 3, 0};
-  WaveStage sh{s_stage[wv][1], L.heavy[p ^ 1], L.counts + 3 + (r + 1) % 3, 0};
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    L.counts[(r + 2) % 3] = 0;
-    L.counts[3 + (r + 2) % 3] = 0;
+  int c = jp_plane_free<64>(s, v);
+  const JpUnit<V> u(g, sd, v, it, lvl);
+  if (c < 0) c = jp_scan_free<NW>(u, lane, 64, s.colour, 64 * s.planes, bits, WaveLdsSync());
+  if (lane == 0) __hip_atomic_store(s.colour + v, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int64_t len = u.len();
+  int32_t low[kJpTurns];   // the first entries stay in registers
+  for (int64_t e0 = 0; e0 < len; e0 += 64 * kJpTurns) {
+    int32_t x[kJpTurns];
+#pragma unroll
+    for (int k = 0; k < kJpTurns; k++) x[k] = u.lower(e0 + 64 * k + lane);
+#pragma unroll
+    for (int k = 0; k < kJpTurns; k++) {
+      if (x[k] >= 0) jp_mark(s, x[k], c);
+      if (e0 == 0) low[k] = x[k];
+    }
   }
-  for (int64_t idx = (int64_t)blockIdx.x * 4 + wv; idx < nf; idx += (int64_t)gridDim.x * 4)
-    jp_unit(g, sd, (int64_t)L.light[p][idx], colour, cnt, sl, sh, it, lvl, s_light[wv]);
-  for (int64_t idx = blockIdx.x; idx < nh; idx += gridDim.x)
-    jp_unit_block(g, sd, (int64_t)L.heavy[p][idx], colour, cnt, sl, sh, it, lvl, s_block);
-  sl.flush();
-  sh.flush();
+  wave_drain();
+  for (int64_t e0 = 0; e0 < len; e0 += 64 * kJpTurns) {
+    int32_t x[kJpTurns];
+    bool ready[kJpTurns];
+#pragma unroll
+    for (int k = 0; k < kJpTurns; k++) {
+      x[k] = e0 == 0 ? low[k] : u.lower(e0 + 64 * k + lane);
+      ready[k] = x[k] >= 0 && atomicSub(s.cnt + x[k], 1u) == 1u;
+    }
+#pragma unroll
+    for (int k = 0; k < kJpTurns; k++)
+      if (__ballot(ready[k])) put(ready[k], x[k]);
+  }
+}
+
+// Colour one unit with the whole block (all threads must call this).
+constexpr int kJpBlockWords = 64;
+template <class V>
+__device__ inline void jp_block(const V &g, const SolveDev &sd, int64_t v, const JpState &s,
+                                WaveStage &st, int it, int lvl, uint64_t *bits) {
+  const int tid = threadIdx.x, nt = blockDim.x;
+  int c = jp_plane_free<64>(s, v);   // v's bitmap is complete: every wave finds the same
+  const JpUnit<V> u(g, sd, v, it, lvl);
+  if (c < 0)
+    c = jp_scan_free<kJpBlockWords>(u, tid, nt, s.colour, 64 * s.planes, bits, BlockLdsSync());
+  if (tid == 0) __hip_atomic_store(s.colour + v, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int64_t len = u.len();
+  for (int64_t e = tid; e < len; e += nt) {
+    const int32_t x = u.lower(e);
+    if (x >= 0) jp_mark(s, x, c);
+  }
+  wave_drain();
+  __syncthreads();   // thread 0's colour is stored as well
+  for (int64_t e0 = 0; e0 < len; e0 += nt) {
+    const int32_t x = u.lower(e0 + tid);
+    st.append(x >= 0 && atomicSub(s.cnt + x, 1u) == 1u, x);
+  }
+}
+
+// One round with its frontier size read on the device, so rounds can be launched back to back
+// without a host round trip: round r colours the list of parity r&1 (counts[r%3] units), appends
+// the released units to the other list (counts[(r+1)%3]) and clears counts[(r+2)%3].  A round
+// with an empty frontier does nothing.
+constexpr int kJpGroup = 8;        // lanes of a short row
+constexpr int kJpGroupRow = 64;     // entries a lane group takes
+constexpr int kJpWaveRow = 256;     // entries a wave takes
+constexpr int kJpWaveWords = (kJpWaveRow + 64) / 64;   // its colour lies within these bitmap words
+constexpr int kJpLater = 256;       // rows a block sets aside for its waves, or for all of it
+template <class V>
+__global__ __launch_bounds__(256) void k_jp_round(V g, SolveDev sd, JpLists L, JpState s, int r,
+                                                  int it, int lvl) {
+  __shared__ uint64_t s_wave[4][kJpWaveWords];
+  __shared__ uint64_t s_block[kJpBlockWords];
+  __shared__ int32_t s_stage[4][kStage];
+  __shared__ int32_t s_mid[kJpLater], s_big[kJpLater];
+  __shared__ uint32_t s_nmid, s_nbig;
+  const int64_t nf = L.counts[r % 3];
+  const int32_t *list = L.list[r & 1];
+  if (blockIdx.x == 0 && threadIdx.x == 0) L.counts[(r + 2) % 3] = 0;
+  if ((int64_t)blockIdx.x * 4 >= nf) return;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  WaveStage st{s_stage[wv], L.list[(r & 1) ^ 1], L.counts + (r + 1) % 3, 0};
+  if (threadIdx.x == 0) s_nmid = s_nbig = 0;
+  __syncthreads();
+  const int64_t waves = (int64_t)gridDim.x * 4, w0 = (int64_t)blockIdx.x * 4 + wv;
+  auto put = [&](bool ready, int32_t x) { st.append(ready, x); };
+  auto later = [&](int32_t *q, uint32_t *n, int32_t v) {   // one lane; full: the next round's
+    const uint32_t i = atomicAdd(n, 1u);
+    if (i < kJpLater) q[i] = v;
+    return i < kJpLater;
+  };
+  if (nf > 2 * waves) {
+    constexpr int kPer = 64 / kJpGroup;
+    const int gl = lane & (kJpGroup - 1);
+    for (int64_t i0 = w0 * kPer; i0 < nf; i0 += waves * kPer) {
+      const int64_t i = i0 + lane / kJpGroup;
+      bool on = i < nf, back = false;
+      const int64_t v = on ? list[i] : list[i0];
+      const JpUnit<V> u(g, sd, v, it, lvl);
+      if (on && u.len() > kJpGroupRow) {
+        if (gl == 0)
+          back = u.len() > kJpWaveRow ? !later(s_big, &s_nbig, (int32_t)v)
+                                      : !later(s_mid, &s_nmid, (int32_t)v);
+        on = false;
+      }
+      const int c = jp_plane_free<kJpGroup>(s, v);
+      if (on && c < 0) {   // beyond the planes: a wave scans the row
+        if (gl == 0) back = !later(s_mid, &s_nmid, (int32_t)v);
+        on = false;
+      }
+      constexpr int kTurns = kJpGroupRow / kJpGroup;
+      int32_t low[kTurns];
+      if (on && gl == 0)
+        __hip_atomic_store(s.colour + v, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+      for (int k = 0; k < kTurns; k++) low[k] = on ? u.lower(k * kJpGroup + gl) : -1;
+#pragma unroll
+      for (int k = 0; k < kTurns; k++)
+        if (low[k] >= 0) jp_mark(s, low[k], c);
+      wave_drain();
+      bool ready[kTurns];
+#pragma unroll
+      for (int k = 0; k < kTurns; k++)
+        ready[k] = low[k] >= 0 && atomicSub(s.cnt + low[k], 1u) == 1u;
+#pragma unroll
+      for (int k = 0; k < kTurns; k++) st.append(ready[k], low[k]);
+      st.append(back, (int32_t)v);
+    }
+  } else {
+    for (int64_t i = w0; i < nf; i += waves) {
+      const int64_t v = list[i];
+      if (g.degree(v) <= kJpWaveRow) {
+        jp_wave<kJpWaveWords>(g, sd, v, s, it, lvl, s_wave[wv], put);
+        continue;
+      }
+      bool back = false;
+      if (lane == 0) back = !later(s_big, &s_nbig, (int32_t)v);
+      st.append(back, (int32_t)v);
+    }
+  }
+  __syncthreads();
+  const int nmid = s_nmid < kJpLater ? s_nmid : kJpLater, nbig = s_nbig < kJpLater ? s_nbig : kJpLater;
+  for (int i = wv; i < nmid; i += 4)
+    jp_wave<kJpWaveWords>(g, sd, (int64_t)s_mid[i], s, it, lvl, s_wave[wv], put);
+  for (int i = 0; i < nbig; i++) jp_block(g, sd, (int64_t)s_big[i], s, st, it, lvl, s_block);
+  st.flush();
+}
+
+constexpr int kJpThreads = 512;
+constexpr int kJpWaves = kJpThreads / 64;
+constexpr int kJpDepth = 16;       // links of a chain followed in one round
+constexpr int kJpSlots = 2048;     // units a block may queue in one round
+constexpr int kJpChainRow = 2048;  // longer rows take the block
+constexpr int kJpChainWords = (kJpChainRow + 64) / 64;
+constexpr int kJpUnitBits = 27;    // unit ids stay below 2^32 / 33 < 2^27: the depth sits above
+static_assert(kJpDepth <= 1 << (31 - kJpUnitBits), "unit and depth fit 31 bits: -1 is an empty slot");
+constexpr uint32_t kJpPolls = 1u << 22;   // ends a wave's wait (seconds) should its block stall
+
+// The units queued by the waves of one block (LDS).  Slots are claimed from `tail` on, then
+// filled, and taken from `head` on; `busy` counts the units taken or queued and not finished, so
+// that it is 0 only when no wave of the block can queue another one.
+struct JpQueue {
+  int32_t *slot;   // [kJpSlots], -1: not filled yet
+  uint32_t *head, *tail, *busy, *next;   // next: units of the round's list taken by the block
+  uint32_t *failed;
+
+  // A wave's next unit (depth above bit kJpUnitBits) from the queue, else from the round's list
+  // (positions blockIdx, blockIdx + gridDim, ...), or -1 when the block has nothing left.
+  __device__ int32_t take(const int32_t *list, int64_t n) const {
+    int32_t got = -1;
+    if ((threadIdx.x & 63) == 0) {
+      bool listed = true;   // the list may hold more for this block
+      for (uint32_t polls = 0;; polls++) {
+        const uint32_t h = load(head), t = load(tail);
+        if (h < (t < kJpSlots ? t : kJpSlots)) {
+          if (atomicCAS(head, h, h + 1) != h) continue;
+          while ((got = (int32_t)load((uint32_t *)slot + h)) < 0) {}   // claimed: its owner fills it
+          break;
+        }
+        if (listed) {
+          atomicAdd(busy, 1u);
+          const int64_t i = blockIdx.x + (int64_t)atomicAdd(next, 1u) * gridDim.x;
+          if (i < n) {
+            got = list[i];
+            break;
+          }
+          atomicSub(busy, 1u);
+          listed = false;
+          continue;
+        }
+        if (load(busy) == 0) break;
+        if (polls >= kJpPolls) {
+          atomicOr(failed, 1u);
+          break;
+        }
+        __builtin_amdgcn_s_sleep(1);
+      }
+    }
+    return __shfl(got, 0, 64);
+  }
+  // queue x behind a unit of this block that is not finished; false when the queue is full
+  __device__ bool push(int32_t x, int depth) const {
+    const uint32_t i = atomicAdd(tail, 1u);
+    if (i >= kJpSlots) return false;
+    atomicAdd(busy, 1u);
+    __hip_atomic_store(slot + i, x | (depth << kJpUnitBits), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_WORKGROUP);
+    return true;
+  }
+  __device__ static uint32_t load(const uint32_t *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+};
+
+// A round of a small level: as k_jp_round, and the units that a block releases are coloured in
+// the same launch up to kJpDepth links down (what does not fit goes to the next round).
+template <class V>
+__global__ __launch_bounds__(kJpThreads) void k_jp_chain(V g, SolveDev sd, JpLists L, JpState s,
+                                                         int r, int it, int lvl) {
+  __shared__ uint64_t s_wave[kJpWaves][kJpChainWords];
+  __shared__ uint64_t s_block[kJpBlockWords];
+  __shared__ int32_t s_stage[kJpWaves][kStage];
+  __shared__ int32_t s_slot[kJpSlots], s_big[kJpLater];
+  __shared__ uint32_t s_q[5];
+  const int64_t nf = L.counts[r % 3];
+  if (blockIdx.x == 0 && threadIdx.x == 0) L.counts[(r + 2) % 3] = 0;
+  if (blockIdx.x >= nf) return;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  WaveStage st{s_stage[wv], L.list[(r & 1) ^ 1], L.counts + (r + 1) % 3, 0};
+  for (int i = threadIdx.x; i < kJpSlots; i += kJpThreads) s_slot[i] = -1;
+  if (threadIdx.x < 5) s_q[threadIdx.x] = 0;
+  __syncthreads();
+  const JpQueue q{s_slot, s_q, s_q + 1, s_q + 2, s_q + 3, L.counts + 4};
+  uint32_t *nbig = s_q + 4;
+  for (;;) {
+    const int32_t got = q.take(L.list[r & 1], nf);
+    if (got < 0) break;
+    int64_t v = got & ((1 << kJpUnitBits) - 1);
+    for (int depth = got >> kJpUnitBits; v >= 0; depth++) {
+      int64_t next = -1;
+      if (g.degree(v) > kJpChainRow) {   // set aside for the block, or for the next round
+        uint32_t i = kJpLater;
+        if (lane == 0 && (i = atomicAdd(nbig, 1u)) < kJpLater) s_big[i] = (int32_t)v;
+        st.append(lane == 0 && i >= kJpLater, (int32_t)v);
+      } else {
+        jp_wave<kJpChainWords>(g, sd, v, s, it, lvl, s_wave[wv], [&](bool ready, int32_t x) {
+          if (depth + 1 < kJpDepth) {
+            const uint64_t bal = __ballot(ready);
+            if (next < 0 && bal) {   // this wave goes on with one of them
+              const int first = __builtin_ctzll(bal);
+              next = __shfl(x, first, 64);
+              if (lane == first) ready = false;
+            }
+            if (ready && q.push(x, depth + 1)) ready = false;
+          }
+          st.append(ready, x);
+        });
+      }
+      v = next;
+    }
+    if (lane == 0) atomicSub(q.busy, 1u);   // its chain is done
+  }
+  __syncthreads();
+  const int nb = *nbig < kJpLater ? *nbig : kJpLater;
+  for (int i = 0; i < nb; i++) jp_block(g, sd, (int64_t)s_big[i], s, st, it, lvl, s_block);
+  st.flush();
 }
 
 // sort key of a unit for batching: colour, then degree bin
@@ -2374,258 +2634,6 @@ __global__ void k_gtab_assign(const int32_t *units, int64_t count, const int64_t
                               int64_t *goff) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < count) goff[units[i]] = off[i];
-}
-
-// ------------------------------------------------------------------ small levels in one block
-// For levels with few units the schedule is bounded by launch latency (a hundred colours,
-// two launches per colour and sweep).  One workgroup of 1024 threads then runs the whole
-// phase: Jones-Plassmann colouring, bucketing by colour, and every colour-batched sweep with
-// block barriers between the decisions and the moves of each batch.  The arithmetic and the
-// decisions are the same functions as in the multi-launch path.
-struct SmallCtl {
-  const int32_t *maxsw;    // [J] sweep cap per solve
-  uint8_t *frozen;         // [J] solve takes no further moves at this level
-  uint32_t *moved;         // [J] moves of the current sweep
-  int64_t *sweeps, *moves, *caps;   // [J] per-solve statistics of this level (accumulated)
-  int J;
-  const uint32_t *limit;   // [slices] rebuild threshold of the Sigma sub-tables
-  const uint32_t *nz;      // [slices] key bound after a rebuild
-  int nslices;
-  int64_t tab_total;
-  int smax;                // largest sweep cap of the participating solves
-};
-
-constexpr int kSmallThreads = 1024;
-
-
-constexpr int kSmallWaves = kSmallThreads / 64;
-
-constexpr int kSmallRowThread = 32;   // rows counted by a single thread in a small level
-template <class P, class V, bool kSweeps>
-__global__ __launch_bounds__(kSmallThreads) void k_small_level(
-    V g, SolveDev sd, int64_t n, const int32_t *work, int64_t nwork, uint32_t *comm,
-    SliceTable sig, int32_t *colour, uint32_t *cnt, int32_t *fa, int32_t *fb, int32_t *order,
-    int64_t *start, uint32_t *target, uint32_t *gk, int64_t *gv, int glg, SmallCtl ctl, int it,
-    int lvl, int *ncol_out) {
-  __shared__ uint32_t sk[kSmallWaves][1 << kWaveLg];
-  __shared__ int64_t sv[kSmallWaves][1 << kWaveLg];
-  __shared__ uint16_t sl[kSmallWaves][kWaveMaxDeg];
-  __shared__ int sn[kSmallWaves];
-  __shared__ uint64_t s_bits[kSmallWaves][kJpLightWords];
-  __shared__ int64_t s_part[kSmallThreads];
-  __shared__ uint32_t s_nf, s_nn;
-  __shared__ int s_maxc, s_any, s_rb;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  // ---- colouring: count higher-priority neighbours, then colour ready frontiers
-  if (tid == 0) {
-    s_nf = 0;
-    s_maxc = -1;
-  }
-  __syncthreads();
-  // rows up to kSmallRowThread entries are counted by one thread, longer ones by a wave
-  for (int64_t i = wv; i < nwork; i += kSmallWaves) {
-    const int64_t v = work[i];
-    if (g.degree(v) <= kSmallRowThread) continue;
-    const int j = g.usolve[v];
-    const uint64_t sm = sd.seedmix[j];
-    const int64_t off = sd.uoff[j];
-    const uint64_t hv = priority(sm, it, lvl, 0, (uint32_t)(v - off));
-    typename V::Row row = g.row(v, sd);
-    int64_t c = 0;
-    for (int64_t e = row.lo + lane; e < row.hi; e += 64) {
-      int32_t x = g.col[e];
-      if (g.wt(row, e, x) == 0) continue;
-      if (outranks(priority(sm, it, lvl, 0, (uint32_t)(x - off)), (uint32_t)x, hv, (uint32_t)v)) c++;
-    }
-    for (int m = 32; m >= 1; m >>= 1) c += shfl_xor64(c, m);
-    if (lane == 0) {
-      cnt[v] = (uint32_t)c;
-      colour[v] = -1;
-      if (c == 0) fa[atomicAdd(&s_nf, 1u)] = (int32_t)v;
-    }
-  }
-  for (int64_t i = tid; i < nwork; i += kSmallThreads) {
-    const int64_t v = work[i];
-    if (g.degree(v) > kSmallRowThread) continue;
-    const int j = g.usolve[v];
-    const uint64_t sm = sd.seedmix[j];
-    const int64_t off = sd.uoff[j];
-    const uint64_t hv = priority(sm, it, lvl, 0, (uint32_t)(v - off));
-    typename V::Row row = g.row(v, sd);
-    uint32_t c = 0;
-    for (int64_t e = row.lo; e < row.hi; e++) {
-      int32_t x = g.col[e];
-      if (g.wt(row, e, x) == 0) continue;
-      if (outranks(priority(sm, it, lvl, 0, (uint32_t)(x - off)), (uint32_t)x, hv, (uint32_t)v)) c++;
-    }
-    cnt[v] = c;
-    colour[v] = -1;
-    if (c == 0) fa[atomicAdd(&s_nf, 1u)] = (int32_t)v;
-  }
-  block_sync_global();
-  int32_t *cur = fa, *nxt = fb;
-  while (s_nf > 0) {
-    const uint32_t nf = s_nf;
-    __syncthreads();
-    if (tid == 0) s_nn = 0;
-    __syncthreads();
-    for (uint32_t idx = wv; idx < nf; idx += kSmallWaves) {
-      const int64_t v = cur[idx];
-      const int j = g.usolve[v];
-      const uint64_t sm = sd.seedmix[j];
-      const int64_t off = sd.uoff[j];
-      const uint64_t hv = priority(sm, it, lvl, 0, (uint32_t)(v - off));
-      typename V::Row row = g.row(v, sd);
-      const int result = jp_first_free<kJpLightWords>(g, row, lane, 64, v, sm, off, hv, colour,
-                                                      it, lvl, s_bits[wv], WaveLdsSync());
-      if (lane == 0) {
-        colour[v] = result;
-        atomicMax(&s_maxc, result);
-      }
-      for (int64_t e = row.lo + lane; e < row.hi; e += 64) {
-        int32_t x = g.col[e];
-        if (g.wt(row, e, x) == 0) continue;
-        if (outranks(priority(sm, it, lvl, 0, (uint32_t)(x - off)), (uint32_t)x, hv, (uint32_t)v))
-          continue;
-        if (atomicSub(cnt + x, 1u) == 1u) nxt[atomicAdd(&s_nn, 1u)] = x;
-      }
-    }
-    block_sync_global();
-    if (tid == 0) s_nf = s_nn;
-    int32_t *t = cur;
-    cur = nxt;
-    nxt = t;
-    __syncthreads();
-  }
-  // ---- bucket the units by colour, or by (colour, degree bin) for the multi-launch sweeps
-  const int ncol = s_maxc + 1;
-  const int nkey = kSweeps ? ncol : kBatchSlots * ncol;
-  auto key_of = [&](int64_t v) -> int {
-    return kSweeps ? colour[v] : (colour[v] << kBatchShift) | (int)batch_slot(g, v);
-  };
-  // every hand-over of global memory between waves (plain stores, then atomics or loads of
-  // other waves) goes through block_sync_global: a plain barrier does not wait for stores
-  for (int c = tid; c <= nkey; c += kSmallThreads) start[c] = 0;
-  block_sync_global();
-  for (int64_t i = tid; i < nwork; i += kSmallThreads)
-    atomicAdd(reinterpret_cast<unsigned long long *>(start + key_of(work[i]) + 1), 1ull);
-  block_sync_global();
-  // inclusive prefix sum of the key counts start[1..nkey]: contiguous chunks per thread, the
-  // chunk totals scanned in LDS
-  {
-    int64_t *a = start + 1;
-    const int64_t chunk = (nkey + kSmallThreads - 1) / kSmallThreads;
-    const int64_t c0 = (int64_t)tid * chunk, c1 = c0 + chunk < nkey ? c0 + chunk : nkey;
-    int64_t sum = 0;
-    for (int64_t c = c0; c < c1; c++) sum += a[c];
-    s_part[tid] = sum;
-    __syncthreads();
-    for (int o = 1; o < kSmallThreads; o <<= 1) {
-      const int64_t t = tid >= o ? s_part[tid - o] : 0;
-      __syncthreads();
-      s_part[tid] += t;
-      __syncthreads();
-    }
-    int64_t run = tid ? s_part[tid - 1] : 0;
-    for (int64_t c = c0; c < c1; c++) {
-      run += a[c];
-      a[c] = run;
-    }
-  }
-  if (tid == 0) *ncol_out = ncol;
-  block_sync_global();
-  // scatter: decisions inside a batch are independent and moves commute, so the order of
-  // units inside a colour does not matter
-  for (int c = tid; c < nkey; c += kSmallThreads) cnt[c] = (uint32_t)start[c];
-  block_sync_global();
-  for (int64_t i = tid; i < nwork; i += kSmallThreads) {
-    const int32_t v = work[i];
-    order[atomicAdd(cnt + key_of(v), 1u)] = v;
-  }
-  block_sync_global();
-  if (!kSweeps) return;
-  // ---- colour-batched sweeps
-  LdsTab ltab{sk[wv], sv[wv], kWaveLg, sl[wv], sn + wv};
-  const uint32_t gmask_lg = glg;
-  for (int t = 0; t < ctl.smax; t++) {
-    for (int j = tid; j < ctl.J; j += kSmallThreads) ctl.moved[j] = 0;
-    block_sync_global();
-    const uint32_t fresh_base = (uint32_t)(n * (int64_t)(1 + t));
-    for (int c = 0; c < ncol; c++) {
-      const int64_t lo = start[c], hi = start[c + 1];
-      for (int64_t idx = lo + wv; idx < hi; idx += kSmallWaves) {
-        const int64_t v = order[idx];
-        uint32_t tg;
-        if (g.degree(v) <= kWaveMaxDeg) {
-          tg = lm_unit<P>(WaveGrp(), ltab, g, sd, v, comm, sig, fresh_base,
-                          (typename P::Score *)nullptr, LmCounters{nullptr});
-        } else {
-          GTab gt{gk + ((int64_t)wv << gmask_lg), gv + ((int64_t)wv << gmask_lg), (int)gmask_lg};
-          tg = lm_unit<P>(WaveGrp(), gt, g, sd, v, comm, sig, fresh_base,
-                          (typename P::Score *)nullptr, LmCounters{nullptr});
-        }
-        if (lane == 0) target[idx] = tg;
-      }
-      block_sync_global();
-      for (int64_t idx = lo + tid; idx < hi; idx += kSmallThreads) {
-        const uint32_t C = target[idx];
-        if (C == kNone) continue;
-        const int64_t v = order[idx];
-        const int j = g.usolve[v];
-        if (ctl.frozen[j]) continue;
-        const uint32_t D = comm[v];
-        const int m = g.plen(v);
-        for (int jj = 0; jj < m; jj++) {
-          int gs;
-          int64_t k;
-          g.pent(v, jj, gs, k);
-          tab_add(sig, gs, D, -(int32_t)k);
-          tab_add(sig, gs, C, (int32_t)k);
-        }
-        comm[v] = C;
-        atomicAdd(ctl.moved + j, 1u);
-      }
-      block_sync_global();
-    }
-    // per-solve stopping rules after the sweep
-    if (tid == 0) {
-      s_any = 0;
-      s_rb = 0;
-    }
-    __syncthreads();
-    for (int j = tid; j < ctl.J; j += kSmallThreads) {
-      if (ctl.frozen[j]) continue;
-      ctl.sweeps[j]++;
-      ctl.moves[j] += ctl.moved[j];
-      if (ctl.moved[j] == 0) {
-        ctl.frozen[j] = 1;
-      } else if (t == ctl.maxsw[j] - 1) {
-        ctl.caps[j]++;
-        ctl.frozen[j] = 1;
-      } else {
-        s_any = 1;
-      }
-    }
-    for (int s2 = tid; s2 < ctl.nslices; s2 += kSmallThreads)
-      if (sig.used[s2] > ctl.limit[s2]) s_rb = 1;
-    block_sync_global();
-    if (!s_any) break;
-    if (s_rb) {   // compact the Sigma table: same contents, fewer dead keys
-      for (int64_t i = tid; i < ctl.tab_total; i += kSmallThreads) sig.slots[i] = 0;
-      block_sync_global();
-      for (int64_t v = tid; v < n; v += kSmallThreads) {
-        const int m = g.plen(v);
-        for (int jj = 0; jj < m; jj++) {
-          int gs;
-          int64_t k;
-          g.pent(v, jj, gs, k);
-          tab_add(sig, gs, comm[v], (int32_t)k, false);
-        }
-      }
-      for (int s2 = tid; s2 < ctl.nslices; s2 += kSmallThreads) sig.used[s2] = ctl.nz[s2];
-      block_sync_global();
-    }
-  }
 }
 
 // ------------------------------------------------------------------ work-list segments

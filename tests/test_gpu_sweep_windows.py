@@ -74,3 +74,27 @@ def test_windows_match_oracle(name, make, gamma, omega):
         for k in STAT_KEYS:
             assert r[k] == pr[k], (sv, k)
     g.close()
+
+
+@pytest.mark.parametrize("cliques,size,slices", [(40, 24, 20), (1, 300, 30)],
+                         ids=["chains", "beyond_the_planes"])
+def test_colouring_matches_oracle(cliques, size, slices):
+    """Colourings of more units than a wave, a block or the chip holds at once: many cliques (long
+    chains of priorities side by side) and one of 300 nodes per snapshot, whose colours lie beyond
+    the 64 that level 0 keeps in a bitmap and the 256 of an aggregated level; both above and, by
+    the second solve's coupling-only graph, below the size at which chains are followed."""
+    from paper_2608_03695_amd import mslm
+    n = cliques * size
+    edges = [(c * size + i, c * size + j) for c in range(cliques) for i in range(size)
+             for j in range(i)]
+    for name, per in (("all", [edges] * slices), ("few", [edges] * 2 + [[]] * 2)):
+        tg = gen.from_edge_lists(n, per, name=name)
+        om, oc, ost = oracle.OracleGraph(tg, 1).leiden(1, max_levels=32, max_iterations=1, seed=3)
+        g = mslm.Graph(tg, 1)
+        m, r = g.leiden(1, max_iterations=1, seed=3)
+        g.close()
+        assert np.array_equal(m, om), name
+        assert np.array_equal(r["q_components"], oc), name
+        assert r["colours_level0"] == ost["colours_first"], name
+        for k in STAT_KEYS:
+            assert r[k] == ost[k], (name, k)
