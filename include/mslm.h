@@ -195,10 +195,10 @@ mslm_status mslm_q_exact_variant(const int64_t *q_components, int32_t n_slices, 
  * mslm_batch_leiden uses the one of the graph its first solve names, the server the defaults.
  *   graphs             1: the sweeps of an aggregated level are replayed from a captured HIP graph
  *                      after the second sweep (default 0: plain launches)
- *   latency_units      aggregated levels whose colour batches hold fewer units than this on
- *                      average decide both unit classes in one kernel (64..65536, default 1024)
- *   split_group_units  level 0: batches of at least this many units on average give their
- *                      lane-group units a launch of their own (0..2^30, default 16384)
+ *   latency_units      aggregated levels: colours of fewer than four times this many units are
+ *                      decided in one kernel (64..65536, default 1024)
+ *   split_group_units  level 0: colours of at least this many units have kernels of their own
+ *                      for lane-group, wave and block units (0..2^30, default 16384)
  *   copy_moves         level 0: the per-entry neighbour-label copy is kept through sweeps that
  *                      moved at most (units / copy_moves) units (1..2^30, default 1024)
  *   lat_parts_max      a sweep decides at least this many times 32 blocks of work ahead of the

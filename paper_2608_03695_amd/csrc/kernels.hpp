@@ -43,9 +43,34 @@ struct SolveDev {
   // were captured once); nullptr: the base passed to the kernel
   const uint32_t *fresh;
   int32_t mark = 0;                    // what a near-tie writes into redo
+  // sweeps that keep track of units at rest (Rest), else nullptr; the counters they are measured
+  // against: per Sigma slice the degree moved, then from index nsl on per solve the degree moved
+  // over the slices' totals in units of 2^-32, summed over the slices
+  struct Rest *rest = nullptr;
+  int64_t *ctr = nullptr;
+  int nsl = 0;
 };
 constexpr int kRedoByte = 0x7f;
 constexpr int32_t kRedoUnset = 0x7f7f7f7f;   // four equal bytes: set by a byte fill
+
+// A unit at rest.  A unit that stays is compared with its best target by q*W - p*b*sum_s k_s y_s/S_s,
+// and of this only the y (Sigma values) change while none of its neighbours moves: a target's y_s
+// falls and the own community's rises by at most the slice-s degree that moves anywhere.  So with
+// `slack` between staying and the best target the unit goes on staying while
+// 2 p b k dM <= slack, dM the degree moved in its slice since (or, spanning several slices,
+// 2 p b max_s(k_s) sum_s dM_s / S_s <= slack); targets that were pruned by q*W alone stay below the
+// best of that time.  `limit` is the counter value up to which that holds, rounded down; a
+// neighbour's move sets it to -1.  Skipping such units changes no decision.
+struct Rest {
+  int64_t limit;
+  int32_t ctr;    // the counter: the unit's Sigma slice, or nsl + solve
+  int32_t pad;
+};
+__device__ inline bool at_rest(const SolveDev &sd, int64_t v) {
+  if (!sd.rest) return false;
+  const Rest r = sd.rest[v];
+  return sd.ctr[r.ctr] <= r.limit;
+}
 
 __device__ inline uint32_t fresh_of(const SolveDev &sd, uint32_t fresh_base) {
   return sd.fresh ? *sd.fresh : fresh_base;
@@ -230,6 +255,27 @@ __device__ inline UnitCtx unit_ctx(const V &g, const SolveDev &sd, int64_t v, ui
   return u;
 }
 
+// Record how long unit v (decided `out`, one thread) stays at rest; kmax: its largest profile
+// degree when it spans several slices.  Rounded down by 2^-30, far above the rounding of the
+// doubles involved.
+__device__ inline void settle(const SolveDev &sd, const UnitCtx &u, uint32_t out, double slack,
+                              double kmax) {
+  if (!sd.rest) return;
+  Rest r{-1, 0, 0};
+  if (out == kNone && slack >= 0.0) {
+    const bool one = u.m <= 1;
+    r.ctr = one ? (u.m ? u.gs0 : 0) : sd.nsl + u.j;
+    const double den = 2.0 * (double)u.pb * (one ? (double)u.k0 : kmax);
+    if (den == 0.0) {
+      r.limit = INT64_MAX;
+    } else {
+      const double room = slack / den * (one ? 1.0 : 0x1p32) * (1.0 - 0x1p-30);
+      r.limit = sd.ctr[r.ctr] + (int64_t)(room < 0x1p61 ? room : 0x1p61);
+    }
+  }
+  sd.rest[u.v] = r;
+}
+
 __device__ inline int64_t target_y(const SliceTable &tab, int gs, int64_t k, uint32_t lab, int kind) {
   if (kind == kEmpty) return 0;
   int64_t y = tab_get(tab, gs, lab);
@@ -273,6 +319,11 @@ struct Policy0 {
     o.g = shfl_xor64(s.g, m);
     o.lab = shfl_xor32(s.lab, m);
     return o;
+  }
+  // how far staying is ahead of the best target (never above the true difference by more than
+  // rounding, which settle() allows for)
+  __device__ static double slack(const UnitCtx &, const Score &stay, const Score &best, int64_t) {
+    return (double)(stay.g - best.g);
   }
   // the score of staying when the Sigma of the unit's own community is already known
   __device__ static Score stay_from(const UnitCtx &u, uint32_t D, int64_t W, int64_t yD) {
@@ -409,6 +460,18 @@ struct PolicyKT {
     else
       return exact_cmp_flag(g, u, sd, tab, a.lab, a.kind & 3, a.W, b.lab, b.kind & 3, b.W);
   }
+  // Without the exact path the best may be one of several targets too close to order.  Their
+  // weights are at most Wmax and their estimates at least about 0 (the empty community's), so each
+  // one's error is at most tie = (m + 8) 2^-49 q Wmax (1 + tiny), and a better one among them lies
+  // within 2 (best.er + tie) + tie of the best's estimate.  Wmax < 0: unknown.
+  __device__ static double slack(const UnitCtx &u, const Score &stay, const Score &best,
+                                 int64_t Wmax) {
+    if (u.m <= 1) return (double)(stay.ex - best.ex);
+    const double d = (stay.ap - stay.er) - (best.ap + best.er);
+    if (Exact) return d;
+    if (Wmax < 0) return -1.0;
+    return d - best.er - 4.0 * (double)(u.m + 8) * 0x1p-49 * (double)u.q * (double)Wmax;
+  }
   __device__ static bool prunable(const UnitCtx &u, int64_t W, const Score &best) {
     if (u.m <= 1) {
       i128 ub = (i128)u.q * W * (u.m ? u.S0 : 1);
@@ -466,6 +529,9 @@ struct PolicyK1 {
                             const Score &a, const Score &b) {
     return a.ex < b.ex ? -1 : (a.ex > b.ex ? 1 : 0);
   }
+  __device__ static double slack(const UnitCtx &, const Score &stay, const Score &best, int64_t) {
+    return (double)(stay.ex - best.ex);
+  }
   __device__ static bool prunable(const UnitCtx &u, int64_t W, const Score &best) {
     i128 ub = (i128)u.q * W * (u.m ? u.S0 : 1);
     return ub < best.ex;
@@ -480,6 +546,19 @@ struct PolicyK1 {
     return o;
   }
 };
+
+// largest profile degree of a unit spanning several slices (one thread)
+template <class V>
+__device__ inline double profile_max(const V &g, const UnitCtx &u) {
+  int64_t best = u.k0;
+  for (int jj = 1; jj < u.m; jj++) {
+    int gs;
+    int64_t k;
+    g.pent(u.v, jj, gs, k);
+    best = k > best ? k : best;
+  }
+  return (double)best;
+}
 
 template <class P, class V>
 __device__ inline bool better(const V &g, const UnitCtx &u, const SolveDev &sd, const SliceTable &tab,
@@ -797,6 +876,11 @@ __device__ inline uint32_t lm_unit_coop(Grp grp, Tab tab, const V &g, const Solv
   uint32_t out = kNone;
   if (P::cmp(g, u, sd, sig, best, stay) > 0)
     out = best.lab == kNone ? fresh_of(sd, fresh_base) + (uint32_t)g.orig(u.v) : best.lab;
+  if (sd.rest) {
+    double kmax = (double)c.k;
+    for (int o = 1; o < c.mp; o <<= 1) kmax = fmax(kmax, __shfl_xor(kmax, o, 64));
+    if (r == 0) settle(sd, u, out, P::slack(u, stay, best, hW > 0 ? hW : 0), kmax);
+  }
   grp.sync();
   return out;
 }
@@ -808,6 +892,7 @@ __device__ inline uint32_t lm_unit(Grp grp, Tab tab, const V &g, const SolveDev 
                                    uint32_t *sredL = nullptr) {
   const int r = grp.rank(), gsz = grp.size();
   if (sd.frozen && sd.frozen[g.solve_of(v)]) return kNone;   // its solve is out of this sweep
+  if (at_rest(sd, v)) return kNone;
   for (int i = r; i < tab.size(); i += gsz) {
     tab.K[i] = 0;
     tab.V[i] = 0;
@@ -873,6 +958,8 @@ __device__ inline uint32_t lm_unit(Grp grp, Tab tab, const V &g, const SolveDev 
   uint32_t out = kNone;
   if (P::cmp(g, u, sd, sig, best, stay) > 0)
     out = best.lab == kNone ? fresh_of(sd, fresh_base) + (uint32_t)g.orig(v) : best.lab;
+  if (r == 0 && sd.rest)
+    settle(sd, u, out, P::slack(u, stay, best, hW > 0 ? hW : 0), profile_max(g, u));
   grp.sync();
   return out;
 }
@@ -952,7 +1039,7 @@ __device__ inline void lm_group_block(const V &g, const SolveDev &sd, const int3
   const int idx = threadIdx.x / G;
   if (idx >= count) return;   // whole groups leave together; shuffles stay inside a group
   const int64_t v = g.unit_at(units, pos + idx);
-  if (sd.frozen && sd.frozen[g.solve_of(v)]) {   // its solve is out of this sweep
+  if ((sd.frozen && sd.frozen[g.solve_of(v)]) || at_rest(sd, v)) {   // nothing to decide
     if (gl == 0) em.target[pos + idx] = kNone;
     return;
   }
@@ -1021,9 +1108,14 @@ __device__ inline void lm_group_block(const V &g, const SolveDev &sd, const int3
     typename P::Score s = P::make(g, u, sd, sig, c, wsum, kTarget);
     if (better<P>(g, u, sd, sig, s, best)) best = s;
   }
+  int64_t Wmax = cand ? wsum : 0;   // largest weight to a candidate
   for (int m = G / 2; m >= 1; m >>= 1) {
     typename P::Score o = P::shfl(best, m);
     if (better<P>(g, u, sd, sig, o, best)) best = o;
+    if (IsMulti<P>::value && sd.rest) {
+      const int64_t w2 = shfl_xor64(Wmax, m);
+      Wmax = w2 > Wmax ? w2 : Wmax;
+    }
   }
   if (pc.c) {
     unsigned long long nc = __popcll(__ballot(cand) & (((G == 64) ? ~0ull : ((1ull << G) - 1)) << gbase));
@@ -1041,6 +1133,7 @@ __device__ inline void lm_group_block(const V &g, const SolveDev &sd, const int3
     if (P::cmp(g, u, sd, sig, best, stay) > 0)
       out = best.lab == kNone ? fresh_of(sd, fresh_base) + (uint32_t)g.orig(v) : best.lab;
     em.put(pos + idx, out);
+    if (sd.rest) settle(sd, u, out, P::slack(u, stay, best, Wmax), profile_max(g, u));
   }
 }
 
@@ -1112,7 +1205,7 @@ __device__ inline void lm0_lockstep(const ViewP &g, const SolveDev &sd, int64_t 
     kv[u] = g.k[v];
     gs[u] = g.slice[v];
     js[u] = kOne ? 0 : g.solve_of(v);   // one solve: its constants are uniform
-    if (sd.frozen && sd.frozen[js[u]]) {   // a solve out of this sweep: nothing to decide
+    if ((sd.frozen && sd.frozen[js[u]]) || at_rest(sd, v)) {   // nothing to decide
       if (live[u] && gl == 0) em.target[pos[u]] = kNone;
       live[u] = false;
       hi[u] = lo[u];
@@ -1272,6 +1365,16 @@ __device__ inline void lm0_lockstep(const ViewP &g, const SolveDev &sd, int64_t 
       if (best.g > stay)
         out = best.lab == kNone ? fresh_of(sd, fresh_base) + (uint32_t)g.uid[pos[u]] : best.lab;
       em.put(pos[u], out);
+      if (sd.rest) {
+        UnitCtx uc;
+        uc.v = pos[u];
+        uc.j = j;
+        uc.m = k0 > 0 ? 1 : 0;
+        uc.gs0 = gs[u];
+        uc.k0 = k0;
+        uc.pb = pb;
+        settle(sd, uc, out, (double)(stay - best.g), 0.0);
+      }
     }
     (void)p;
   }
@@ -1289,7 +1392,7 @@ __device__ inline void lm0_lockstep(const ViewP &g, const SolveDev &sd, int64_t 
 // queues pairs of both without waiting; a pair that comes after the last colour does nothing.
 //
 // Work is cut into items of one block each, listed per kernel family in colour order.
-enum { kFamGroup1, kFamGroup, kFamMulti1, kFamMulti, kFamBlock, kFamHub, kFams };
+enum { kFamAll, kFamGroup1, kFamGroup, kFamMulti1, kFamMulti, kFamBlock, kFamHub, kFams };
 
 struct WinItem {
   int32_t pos, count;   // positions [pos, pos + count) of the colour order
@@ -1392,8 +1495,9 @@ __global__ __launch_bounds__(256) void k_win_begin(WinLevel L, int t, uint32_t *
   }
 }
 
-// One block's share of a unit bin: lane groups, waves or the whole block (bins 0..5).
-template <class P, class V>
+// One block's share of a unit bin: lane groups, waves (a table of 512 slots each), or the whole
+// block with a table of 2^11 slots (bin 5) or 2^LG (bin 6).
+template <class P, int LG, class V>
 __device__ inline void win_item(const V &g, const SolveDev &sd, const int32_t *units,
                                 const WinItem &it, const uint32_t *comm, const SliceTable &sig,
                                 const Emit &em, uint32_t fresh_base, LmCounters pc, uint32_t *sk,
@@ -1435,7 +1539,7 @@ __device__ inline void win_item(const V &g, const SolveDev &sd, const int32_t *u
       break;
     }
     default: {
-      LdsTab tab{sk, sv, kSmallBlockLg, sl, sn};
+      LdsTab tab{sk, sv, it.slot % kNumBins == 5 ? kSmallBlockLg : LG, sl, sn};
       const uint32_t out = lm_unit<P>(BlockGrp(), tab, g, sd, g.unit_at(units, it.pos), comm, sig,
                                       fresh_base, red, pc, hw, hl);
       if (threadIdx.x == 0) em.put(it.pos, out);
@@ -1443,9 +1547,15 @@ __device__ inline void win_item(const V &g, const SolveDev &sd, const int32_t *u
   }
 }
 
-// Bins 0..5 of a window: units of class 1 (slots from kNumBins on) by P1, the others by P.
-template <class P, class P1, class V>
-__global__ __launch_bounds__(256) void k_win_multi(V g, SolveDev sd, WinLevel L, int fam, int r,
+// Waves per SIMD that the registers are held to (the exact policy needs scratch anyway): 4 instead
+// of the compiler's 3 took the level-0 kernel of a 3.2M-unit solve from 39.1 to 36.5 ms, 8 instead
+// of 5 the lane-group kernels from 34 to 30 ms; 5 lost to spills.
+template <class P>
+constexpr int kWinWaves = std::is_same<P, PolicyK>::value ? 1 : IsMulti<P>::value ? 3 : 4;
+
+// Bins 4 and 5 of a window's large colours, one class of units.
+template <class P, class V>
+__global__ __launch_bounds__(256, kWinWaves<P>) void k_win_multi(V g, SolveDev sd, WinLevel L, int fam, int r,
                                                    const int32_t *units, const uint32_t *comm,
                                                    SliceTable sig, uint32_t *target,
                                                    uint32_t fresh_base, LmCounters pc) {
@@ -1454,7 +1564,6 @@ __global__ __launch_bounds__(256) void k_win_multi(V g, SolveDev sd, WinLevel L,
   __shared__ uint16_t sl[kSmallBlockMaxDeg];         // 4 lists of 256, or one of 1024
   __shared__ int sn[4];
   __shared__ typename P::Score red[4];
-  __shared__ typename P1::Score red1[4];
   __shared__ int64_t hw[4];
   __shared__ uint32_t hl[4];
   const WinRange w(L, fam, r);
@@ -1465,10 +1574,46 @@ __global__ __launch_bounds__(256) void k_win_multi(V g, SolveDev sd, WinLevel L,
     const WinItem it = L.items[i];
     const Emit em{target, L.first_move + r, it.colour};
     sd.mark = it.colour;
+    win_item<P, kSmallBlockLg>(g, sd, units, it, comm, sig, em, fresh_base, pc, sk, sv, sl, sn, red,
+                               hw, hl);
+    __syncthreads();   // the next item lays its tables over this one's
+  }
+}
+
+// Every bin below the hubs of a window of small colours, in one launch: such windows are bound by
+// latency, and one launch over both classes (units of class 1, slots from kNumBins on, by P1, the
+// others by P) takes the place of up to five in a row.  LG: the rows fill at most half the table;
+// small tables let more blocks share a CU.  Blocks of 512 threads cost the exact policy's levels a
+// quarter (57k units: 67.5 ms against 53.7) and gained a tenth or less elsewhere.
+template <class P, class P1, class V, int LG>
+__global__ __launch_bounds__(256) void k_win_all(V g, SolveDev sd, WinLevel L, int r,
+                                                         const int32_t *units,
+                                                         const uint32_t *comm, SliceTable sig,
+                                                         uint32_t *target, uint32_t fresh_base,
+                                                         LmCounters pc) {
+  static_assert(LG >= 11, "a wave table of 512 slots for each wave");
+  constexpr int kWaves = 4;
+  __shared__ uint32_t sk[1 << LG];
+  __shared__ int64_t sv[1 << LG];
+  __shared__ uint16_t sl[1 << (LG - 1)];
+  __shared__ int sn[kWaves];
+  __shared__ typename P::Score red[kWaves];
+  __shared__ typename P1::Score red1[kWaves];
+  __shared__ int64_t hw[kWaves];
+  __shared__ uint32_t hl[kWaves];
+  const WinRange w(L, kFamAll, r);
+  if (sd.redo) sd.redo = L.near_tie + r * L.J;
+  for (int k = blockIdx.x; k < w.turns(); k += gridDim.x) {
+    const int i = w.item(k);
+    if (i < 0) continue;
+    const WinItem it = L.items[i];
+    const Emit em{target, L.first_move + r, it.colour};
+    sd.mark = it.colour;
     if (!std::is_same<P, P1>::value && it.slot >= kNumBins)
-      win_item<P1>(g, sd, units, it, comm, sig, em, fresh_base, pc, sk, sv, sl, sn, red1, hw, hl);
+      win_item<P1, LG>(g, sd, units, it, comm, sig, em, fresh_base, pc, sk, sv, sl, sn, red1, hw,
+                       hl);
     else
-      win_item<P>(g, sd, units, it, comm, sig, em, fresh_base, pc, sk, sv, sl, sn, red, hw, hl);
+      win_item<P, LG>(g, sd, units, it, comm, sig, em, fresh_base, pc, sk, sv, sl, sn, red, hw, hl);
     __syncthreads();   // the next item lays its tables over this one's
   }
 }
@@ -1476,7 +1621,7 @@ __global__ __launch_bounds__(256) void k_win_multi(V g, SolveDev sd, WinLevel L,
 // Bins 0..3 alone: little LDS, so large batches run at the occupancy the group code's registers
 // allow, where the fused kernel's tables would hold it lower.
 template <class P, class V>
-__global__ __launch_bounds__(256) void k_win_groups(V g, SolveDev sd, WinLevel L, int fam, int r,
+__global__ __launch_bounds__(256, IsMulti<P>::value ? 1 : 8) void k_win_groups(V g, SolveDev sd, WinLevel L, int fam, int r,
                                                     const int32_t *units, const uint32_t *comm,
                                                     SliceTable sig, uint32_t *target,
                                                     uint32_t fresh_base, LmCounters pc) {
@@ -1513,7 +1658,7 @@ __global__ __launch_bounds__(256) void k_win_groups(V g, SolveDev sd, WinLevel L
 // Bins 0..3 of level 0 in position order (lm0_lockstep).  kOne: a single solve; kCopy:
 // neighbour labels from the label copy.
 template <int U, bool kOne, bool kCopy>
-__global__ __launch_bounds__(256) void k_win_lm0(ViewP g, SolveDev sd, WinLevel L, int r,
+__global__ __launch_bounds__(256, 8) void k_win_lm0(ViewP g, SolveDev sd, WinLevel L, int r,
                                                  const uint32_t *comm, SliceTable sig,
                                                  uint32_t *target, uint32_t fresh_base,
                                                  LmCounters pc) {
@@ -1585,12 +1730,14 @@ __global__ __launch_bounds__(NT) void k_win_block(V g, SolveDev sd, WinLevel L, 
 constexpr int kHubBlocks = 16;
 
 template <class V>
-__global__ __launch_bounds__(256) void k_hub_clear(V g, WinLevel L, int r, const int32_t *units,
+__global__ __launch_bounds__(256) void k_hub_clear(V g, SolveDev sd, WinLevel L, int r,
+                                                   const int32_t *units,
                                                    const int64_t *goff, const int32_t *glg,
                                                    uint32_t *gk, int64_t *gv) {
   const WinRange w(L, kFamHub, r);
   for (int y = blockIdx.y; y < w.n; y += gridDim.y) {
     const int64_t v = g.unit_at(units, L.items[w.i0 + y].pos);
+    if (at_rest(sd, v)) continue;
     const int64_t size = 1ll << glg[v], base = goff[v];
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < size;
          i += (int64_t)gridDim.x * blockDim.x) {
@@ -1618,7 +1765,7 @@ __global__ __launch_bounds__(256) void k_hub_accum(V g, SolveDev sd, WinLevel L,
   const WinRange win(L, kFamHub, r);
   for (int y = blockIdx.y; y < win.n; y += gridDim.y) {
     const int64_t v = g.unit_at(units, L.items[win.i0 + y].pos);
-    if (sd.frozen && sd.frozen[g.solve_of(v)]) continue;   // its solve is out of this sweep
+    if ((sd.frozen && sd.frozen[g.solve_of(v)]) || at_rest(sd, v)) continue;   // nothing to decide
     GTab tab{gk + goff[v], gv + goff[v], glg[v]};
     typename V::Row row = g.row(v, sd);
     for (int i = threadIdx.x; i < (1 << kHubLdsLg); i += blockDim.x) {
@@ -1686,7 +1833,7 @@ __global__ __launch_bounds__(256) void k_hub_eval(V g, SolveDev sd, WinLevel L, 
   for (int y = blockIdx.y; y < win.n; y += gridDim.y) {
     const WinItem it = L.items[win.i0 + y];
     const int64_t v = g.unit_at(units, it.pos);
-    if (sd.frozen && sd.frozen[g.solve_of(v)]) continue;
+    if ((sd.frozen && sd.frozen[g.solve_of(v)]) || at_rest(sd, v)) continue;
     sd.mark = it.colour;
     const uint32_t D = comm[v];
     const uint32_t *K = gk + goff[v];
@@ -1771,7 +1918,7 @@ __global__ __launch_bounds__(64) void k_hub_final(V g, SolveDev sd, WinLevel L, 
   for (int y = blockIdx.x; y < win.n; y += gridDim.x) {
     const WinItem it = L.items[win.i0 + y];
     const int64_t v = g.unit_at(units, it.pos);
-    if (sd.frozen && sd.frozen[g.solve_of(v)]) {
+    if ((sd.frozen && sd.frozen[g.solve_of(v)]) || at_rest(sd, v)) {
       if (lane == 0) target[it.pos] = kNone;
       continue;
     }
@@ -1797,20 +1944,43 @@ __global__ __launch_bounds__(64) void k_hub_final(V g, SolveDev sd, WinLevel L, 
       if (P::cmp(g, u, sd, sig, best, stay) > 0)
         out = best.lab == kNone ? fresh_of(sd, fresh_base) + (uint32_t)g.orig(v) : best.lab;
       Emit{target, L.first_move + r, it.colour}.put(it.pos, out);
+      if (sd.rest) settle(sd, u, out, P::slack(u, stay, best, -1), profile_max(g, u));
     }
   }
 }
 
 // Apply the moves of pair r's window (those of its first moving colour): new label, Sigma delta
-// for every profile slice, the label copy of level 0; and set up the next window.  Few units
-// take a wave each, its lanes over the profile slices (up to 64, two Sigma atomics each) or the
-// row; many units take a thread each, the long rows of the movers a wave.  Near-ties of the
-// colours whose decisions count ask for a repeat of their solve's sweep.
+// for every profile slice, the label copy of level 0, the neighbours no longer at rest; and set up
+// the next window.  Few units take a wave each, its lanes over the profile slices (up to 64, two
+// Sigma atomics each) and the row; many units take a thread each, the long rows of the movers a
+// wave.  Near-ties of the colours whose decisions count ask for a repeat of their solve's sweep.
 template <class V>
-__global__ __launch_bounds__(256) void k_win_apply(V g, WinLevel L, int r,
+__device__ inline void apply_sigma(const V &g, const SolveDev &sd, const SliceTable &sig, int64_t v,
+                                   uint32_t D, uint32_t C, int jj, int64_t &share) {
+  int gs;
+  int64_t k;
+  g.pent(v, jj, gs, k);
+  tab_add(sig, gs, D, -(int32_t)k);
+  tab_add(sig, gs, C, (int32_t)k);
+  if (sd.rest) {
+    atomicAdd(reinterpret_cast<unsigned long long *>(sd.ctr + gs), (unsigned long long)k);
+    if (!V::kLevel0) share += (int64_t)((((uint64_t)k << 32) + sd.S[gs] - 1) / (uint64_t)sd.S[gs]);
+  }
+}
+// entry e of a moved unit: its neighbour is not at rest any more, and reads the new label C
+template <class V>
+__device__ inline void apply_entry(const V &g, const SolveDev &sd, int64_t e, uint32_t C) {
+  if (sd.rest) sd.rest[g.col[e] & 0x7fffffff].limit = -1;
+  if constexpr (std::is_same<V, ViewP>::value) {
+    if (g.elab) g.elab[g.prev[e]] = C;
+  }
+}
+
+template <class V>
+__global__ __launch_bounds__(256) void k_win_apply(V g, SolveDev sd, WinLevel L, int r,
                                                    const int32_t *units, const uint32_t *target,
                                                    uint32_t *comm, SliceTable sig,
-                                                   uint32_t *moved, int32_t *redo) {
+                                                   uint32_t *moved) {
   __shared__ uint32_t s_moves;
   const WinState s = L.st[r];
   const int f = L.first_move[r];
@@ -1837,7 +2007,7 @@ __global__ __launch_bounds__(256) void k_win_apply(V g, WinLevel L, int r,
     if (L.near_tie)
       for (int j = threadIdx.x; j < L.J; j += blockDim.x) {
         const int c = L.near_tie[r * L.J + j];
-        if (live && c < s.c1 && c <= f) redo[j] = 0;
+        if (live && c < s.c1 && c <= f) sd.redo[j] = 0;
         L.near_tie[((r + 2) % 3) * L.J + j] = kNoColour;
       }
   }
@@ -1845,6 +2015,8 @@ __global__ __launch_bounds__(256) void k_win_apply(V g, WinLevel L, int r,
   const int lo = L.cptr[f], hi = L.cptr[f + 1];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int waves = gridDim.x * 4;
+  bool rows = sd.rest != nullptr;   // moved units' rows are visited
+  if constexpr (std::is_same<V, ViewP>::value) rows = rows || g.elab;
   if (hi - lo <= 2 * waves) {
     for (int i = lo + blockIdx.x * 4 + wv; i < hi; i += waves) {
       const uint32_t C = target[i];
@@ -1852,20 +2024,18 @@ __global__ __launch_bounds__(256) void k_win_apply(V g, WinLevel L, int r,
       const int64_t v = g.unit_at(units, i);
       const uint32_t D = comm[v];
       const int m = g.plen(v);
-      for (int jj = lane; jj < m; jj += 64) {
-        int gs;
-        int64_t k;
-        g.pent(v, jj, gs, k);
-        tab_add(sig, gs, D, -(int32_t)k);
-        tab_add(sig, gs, C, (int32_t)k);
-      }
-      if constexpr (std::is_same<V, ViewP>::value) {
-        if (g.elab)   // the entries pointing at v see its new label
-          for (int64_t e = g.rp[v] + lane; e < g.rp[v + 1]; e += 64) g.elab[g.prev[e]] = C;
-      }
+      const int j = g.solve_of(v);
+      int64_t share = 0;
+      for (int jj = lane; jj < m; jj += 64) apply_sigma(g, sd, sig, v, D, C, jj, share);
+      if (!V::kLevel0 && sd.rest) share = wave_sum64(share);
+      if (rows)
+        for (int64_t e = g.rp[v] + lane; e < g.rp[v + 1]; e += 64) apply_entry(g, sd, e, C);
       if (lane == 0) {
         comm[v] = C;
-        atomicAdd(moved + g.solve_of(v), 1u);
+        atomicAdd(moved + j, 1u);
+        if (!V::kLevel0 && sd.rest)
+          atomicAdd(reinterpret_cast<unsigned long long *>(sd.ctr + sd.nsl + j),
+                    (unsigned long long)share);
       }
     }
     return;
@@ -1877,40 +2047,33 @@ __global__ __launch_bounds__(256) void k_win_apply(V g, WinLevel L, int r,
     const int i = i0 + lane;
     const uint32_t C = i < hi ? target[i] : kNone;
     const bool mv = C != kNone;
-    int64_t v = 0;
+    int64_t v = 0, share = 0;
     int j = 0;
     if (mv) {
       v = g.unit_at(units, i);
       j = g.solve_of(v);
       const uint32_t D = comm[v];
       const int m = g.plen(v);
-      for (int jj = 0; jj < m; jj++) {
-        int gs;
-        int64_t k;
-        g.pent(v, jj, gs, k);
-        tab_add(sig, gs, D, -(int32_t)k);
-        tab_add(sig, gs, C, (int32_t)k);
-      }
+      for (int jj = 0; jj < m; jj++) apply_sigma(g, sd, sig, v, D, C, jj, share);
       comm[v] = C;
       mine++;
     }
     if (L.J > 1) wave_count(moved, j, mv);
-    if constexpr (std::is_same<V, ViewP>::value) {
-      if (g.elab) {
-        int64_t e0 = 0, e1 = 0;
-        if (mv) {
-          e0 = g.rp[v];
-          e1 = g.rp[v + 1];
-        }
-        const bool wide = e1 - e0 > 16;
-        if (!wide)
-          for (int64_t e = e0; e < e1; e++) g.elab[g.prev[e]] = C;
-        for (uint64_t b = __ballot(wide); b; b &= b - 1) {
-          const int l = __builtin_ctzll(b);
-          const int64_t a0 = __shfl(e0, l, 64), a1 = __shfl(e1, l, 64);
-          const uint32_t c = (uint32_t)__shfl((int)C, l, 64);
-          for (int64_t e = a0 + lane; e < a1; e += 64) g.elab[g.prev[e]] = c;
-        }
+    if (!V::kLevel0 && sd.rest) wave_add64(sd.ctr + sd.nsl, j, share);
+    if (rows) {
+      int64_t e0 = 0, e1 = 0;
+      if (mv) {
+        e0 = g.rp[v];
+        e1 = g.rp[v + 1];
+      }
+      const bool wide = e1 - e0 > 16;
+      if (!wide)
+        for (int64_t e = e0; e < e1; e++) apply_entry(g, sd, e, C);
+      for (uint64_t b = __ballot(wide); b; b &= b - 1) {
+        const int l = __builtin_ctzll(b);
+        const int64_t a0 = __shfl(e0, l, 64), a1 = __shfl(e1, l, 64);
+        const uint32_t c = (uint32_t)__shfl((int)C, l, 64);
+        for (int64_t e = a0 + lane; e < a1; e += 64) apply_entry(g, sd, e, c);
       }
     }
   }

@@ -1,8 +1,9 @@
 """GPU: sweeps decide windows of several colours at once; memberships, Q components and the
 schedule's statistics must equal the oracle's where a window can go wrong: more colours than a
 wave has lanes, hub units (above the block table's 4096 entries) between ordinary ones, windows
-as narrow and as wide as the tuning allows, one kernel for both unit classes or one each, and
-unions of solves that stop at different sweeps."""
+as narrow and as wide as the tuning allows, one kernel for both unit classes or one each, tables
+of every size, sweeps that skip units at rest, and unions of solves that stop at different
+sweeps."""
 from fractions import Fraction as F
 
 import numpy as np
@@ -30,21 +31,26 @@ def _dense():
     return gen.from_edge_lists(420, slices, name="cliques")
 
 
-def _hubs():
-    """Two nodes joined to most others, in a graph of small communities."""
+def _hubs(degrees=(5200, 5200)):
+    """Nodes of many neighbours in a graph of small communities."""
     base = gen.dcsbm(6000, 2, 6, 60, 0.2, 2.5, 0.05, seed=5)
     rng = np.random.default_rng(4)
     slices = []
     for s in range(2):
         u, x, _ = base.slice_edges(s)
         edges = [(int(a), int(b)) for a, b in zip(u, x)]
-        for hub in (0, 1):
-            edges += [(hub, int(b)) for b in rng.choice(np.arange(2, 6000), 5200, replace=False)]
+        for hub, d in enumerate(degrees):
+            edges += [(hub, int(b)) for b in rng.choice(np.arange(len(degrees), 6000), d,
+                                                             replace=False)]
         slices.append(edges)
     return gen.from_edge_lists(6000, slices, name="hubs")
 
 
-GRAPHS = [("dense", _dense, F(1), F(1, 2)), ("hubs", _hubs, F(2), F(1))]
+GRAPHS = [("dense", _dense, F(1), F(1, 2)), ("hubs", _hubs, F(2), F(1)),
+          # rows at the edges of the 2048-, 4096- and 8192-slot tables (a node's degree is about
+          # its base degree above these)
+          ("rows_2k", lambda: _hubs((1015, 1020, 1500, 1900)), F(2), F(1, 8)),
+          ("rows_4k", lambda: _hubs((1015, 2030, 2045, 3900)), F(1, 2), F(1, 4))]
 TUNINGS = [dict(), dict(lat_parts_max=1), dict(latency_units=64, split_group_units=0),
            dict(latency_units=65536, split_group_units=1 << 30, lat_parts_max=2)]
 
