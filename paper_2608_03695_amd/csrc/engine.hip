@@ -90,7 +90,7 @@ struct Workspace {
   // union level 0
   Buf u_rp, u_col, u_w, u_k, u_uslice, u_usolve, u_sstart, u_pmap, u_rev;
   // per solve / per slice
-  Buf s_p, s_q, s_pb, s_a, s_b, s_seed, s_uoff, s_sfirst, s_slast, s_S, s_frozen, s_cnt, s_cnt2;
+  Buf s_p, s_q, s_pb, s_a, s_b, s_seed, s_uoff, s_sfirst, s_slast, s_S, s_rS, s_frozen, s_cnt, s_cnt2;
   Buf fallbacks;
   // state
   Buf pcur, pnew, comm, comm2, map0, pflat, parent, isroot, rank0;

@@ -31,6 +31,12 @@ struct SolveDev {
   const int64_t *uoff;                 // first unit of the solve at the current level
   const int32_t *sfirst;               // first global slice of the solve
   const int64_t *S;                    // per global slice: 2m_s, or 1 for an empty slice
+  // doubles of the multi-slice estimates: values are scaled by L, the least common multiple of the
+  // solve's S when it is below 2^53 (else 1).  rS: per global slice L/S (an integer then);
+  // scale: per solve L, then from index J on the bound below which a scaled value is exact (2^53,
+  // or 0 when L is not used)
+  const double *rS, *scale;
+  int J;
   int64_t *fallbacks;                  // exact-comparison counter per solve
   // per solve: the smallest mark of a near-tie that a kernel without the big-integer path could
   // not settle (kRedoUnset: none).  Refinement marks 0; a window of colours marks the unit's
@@ -236,6 +242,7 @@ struct UnitCtx {
   int gs0;        // first profile slice
   int64_t k0;     // first profile degree
   int64_t p, q, pb, S0;
+  double scale, lim;   // of the multi-slice estimates (SolveDev)
 };
 
 template <class V>
@@ -252,6 +259,8 @@ __device__ inline UnitCtx unit_ctx(const V &g, const SolveDev &sd, int64_t v, ui
   u.q = sd.q[u.j];
   u.pb = sd.pb[u.j];
   u.S0 = u.m > 0 ? sd.S[u.gs0] : 1;
+  u.scale = sd.scale[u.j];
+  u.lim = sd.scale[sd.J + u.j];
   return u;
 }
 
@@ -432,7 +441,7 @@ struct PolicyKT {
         int64_t k;
         g.pent(u.v, jj, gs, k);
         int64_t y = target_y(tab, gs, k, lab, kind);
-        double t = (double)(k * y) / (double)sd.S[gs];
+        double t = (double)(k * y) * sd.rS[gs];
         acc += t;
         mag += fabs(t);
       }
@@ -440,11 +449,14 @@ struct PolicyKT {
     }
     return s;
   }
-  // estimate and error bound from the summed null terms (any summation order)
+  // estimate and error bound from the summed null terms (any summation order).  With the solve's
+  // common denominator every operand and partial sum is an integer, and no larger than `all`:
+  // below 2^53 nothing was rounded.
   __device__ static void finish(const UnitCtx &u, int64_t W, double acc, double mag, Score &s) {
-    double qw = (double)u.q * (double)W;
+    const double qw = (double)u.q * (double)W * u.scale;
+    const double all = fabs(qw) + (double)u.pb * mag;
     s.ap = qw - (double)u.pb * acc;
-    s.er = (double)(u.m + 8) * 0x1p-50 * (fabs(qw) + (double)u.pb * mag);
+    s.er = all < u.lim ? 0.0 : (double)(u.m + 8) * 0x1p-50 * all;
     if (mag == 0.0 || u.pb == 0) s.kind |= 4;
   }
   template <class V>
@@ -455,6 +467,7 @@ struct PolicyKT {
     if ((a.kind & 4) && (b.kind & 4)) return a.W < b.W ? -1 : (a.W > b.W ? 1 : 0);   // both q*W
     double d = a.ap - b.ap;
     if (fabs(d) > 2.0 * (a.er + b.er)) return d > 0 ? 1 : -1;
+    if (a.er + b.er == 0.0) return 0;   // both exact
     if constexpr (Exact)
       return exact_cmp(g, u, sd, tab, a.lab, a.kind & 3, a.W, b.lab, b.kind & 3, b.W);
     else
@@ -467,10 +480,10 @@ struct PolicyKT {
   __device__ static double slack(const UnitCtx &u, const Score &stay, const Score &best,
                                  int64_t Wmax) {
     if (u.m <= 1) return (double)(stay.ex - best.ex);
-    const double d = (stay.ap - stay.er) - (best.ap + best.er);
+    const double d = ((stay.ap - stay.er) - (best.ap + best.er)) / u.scale;
     if (Exact) return d;
     if (Wmax < 0) return -1.0;
-    return d - best.er - 4.0 * (double)(u.m + 8) * 0x1p-49 * (double)u.q * (double)Wmax;
+    return d - best.er / u.scale - 4.0 * (double)(u.m + 8) * 0x1p-49 * (double)u.q * (double)Wmax;
   }
   __device__ static bool prunable(const UnitCtx &u, int64_t W, const Score &best) {
     if (u.m <= 1) {
@@ -478,7 +491,7 @@ struct PolicyKT {
       return ub < best.ex;
     }
     // q*W rounded up versus a rigorous lower bound of the best value
-    double ub = (double)u.q * (double)W * (1.0 + 0x1p-48);
+    double ub = (double)u.q * (double)W * u.scale * (1.0 + 0x1p-48);
     return ub < best.ap - best.er;
   }
   __device__ static Score shfl(const Score &s, int m) {
@@ -720,7 +733,7 @@ struct CoopLane {
   int j;           // this lane's slice index within the profile (valid when j < m)
   bool valid;
   int64_t k;       // unit degree in that slice
-  double S;        // slice denominator
+  double r;        // that slice's scaled 1/S
   const uint64_t *sub;
   uint32_t mask;
   int shift;
@@ -734,14 +747,14 @@ __device__ inline CoopLane coop_lane(const V &g, const UnitCtx &u, const SolveDe
   c.j = rank & (c.mp - 1);
   c.valid = c.j < u.m;
   c.k = 0;
-  c.S = 1.0;
+  c.r = 0.0;
   c.sub = tab.slots;
   c.mask = 0;
   c.shift = 32;
   if (c.valid) {
     int gs;
     g.pent(u.v, c.j, gs, c.k);
-    c.S = (double)sd.S[gs];
+    c.r = sd.rS[gs];
     c.shift = tab.shift[gs];
     c.mask = 0xffffffffu >> c.shift;
     c.sub = tab.slots + tab.base[gs];
@@ -791,7 +804,7 @@ __device__ inline ScoreK coop_score(const UnitCtx &u, const CoopLane &c, uint32_
   double t = 0.0;
   if (c.valid && kind != kEmpty) {
     if (kind == kStay) y -= c.k;
-    t = (double)(c.k * y) / c.S;
+    t = (double)(c.k * y) * c.r;
   }
   double acc = t, mag = fabs(t);
   for (int o = 1; o < c.mp; o <<= 1) {
@@ -2939,7 +2952,7 @@ __global__ __launch_bounds__(256) void k_ref_wc(V g, SolveDev sd, const int32_t 
       c0 = c;
     }
     m++;
-    double t = (double)c / (double)sd.S[gs];
+    double t = (double)c * sd.rS[gs];
     acc += t;
     mag += fabs(t);
   }
@@ -2950,10 +2963,13 @@ __global__ __launch_bounds__(256) void k_ref_wc(V g, SolveDev sd, const int32_t 
   } else if (mag == 0.0 || pb == 0) {
     sign = ext[T] > 0 ? 1 : (ext[T] < 0 ? -1 : 0);
   } else {
-    double qw = (double)q * (double)ext[T];
-    double ap = qw - (double)pb * acc;
-    double er = (double)(m + 8) * 0x1p-50 * (fabs(qw) + (double)pb * mag);
-    if (fabs(ap) > er) {
+    const double qw = (double)q * (double)ext[T] * sd.scale[j];
+    const double all = fabs(qw) + (double)pb * mag;
+    const double ap = qw - (double)pb * acc;
+    const double er = all < sd.scale[sd.J + j] ? 0.0 : (double)(m + 8) * 0x1p-50 * all;
+    if (er == 0.0) {   // exact: one common denominator
+      sign = ap > 0 ? 1 : (ap < 0 ? -1 : 0);
+    } else if (fabs(ap) > er) {
       sign = ap > 0 ? 1 : -1;
     } else {
       atomicAdd(reinterpret_cast<unsigned long long *>(sd.fallbacks + j), 1ull);

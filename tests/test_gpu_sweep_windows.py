@@ -104,3 +104,30 @@ def test_colouring_matches_oracle(cliques, size, slices):
         assert r["colours_level0"] == ost["colours_first"], name
         for k in STAT_KEYS:
             assert r[k] == ost[k], (name, k)
+
+
+@pytest.mark.parametrize("weight", [1, 1 << 10, 1 << 14, 1 << 18])
+def test_common_denominators_match_oracle(weight):
+    """Graphs full of exact ties (rings of equal cliques), with edge weights that take the values
+    of targets, scaled by the slices' common denominator, from far below 2^53 (where doubles are
+    exact) to beyond it, and slice totals with small and with large common multiples."""
+    from paper_2608_03695_amd import mslm
+    for extra in ((0, 0, 0), (0, 1, 5), (2, 3, 7)):
+        slices = []
+        for s in range(3):
+            edges = [(c * 8 + i, c * 8 + j, weight) for c in range(15) for i in range(8)
+                     for j in range(i)]
+            edges += [(c * 8, (c * 8 + 9) % 120, weight) for c in range(15)]
+            edges += [(c * 8 + 3, (c * 8 + 23) % 120, weight) for c in range(extra[s])]
+            slices.append(edges)
+        tg = gen.from_edge_lists(120, slices, weighted=True, name="ring")
+        for omega, kw in ((F(1), {}), (F(1, 2), dict(gamma=F(1, 20), null_model=2))):
+            om, oc, ost = oracle.OracleGraph(tg, omega).leiden(max_levels=32, max_iterations=2,
+                                                               seed=1, **kw)
+            g = mslm.Graph(tg, omega)
+            m, r = g.leiden(max_iterations=2, seed=1, **kw)
+            g.close()
+            assert np.array_equal(m, om), (extra, omega)
+            assert np.array_equal(r["q_components"], oc), (extra, omega)
+            for k in STAT_KEYS:
+                assert r[k] == ost[k], (extra, omega, k)
