@@ -2,7 +2,9 @@
 // key/value pairs, and reduce-by-key over sorted keys.
 //
 // Scan: every block reduces a tile, one block scans the tile sums, every block rescans its
-// tile with its offset (read twice, written once).
+// tile with its offset (read twice, written once).  Up to kFoldSums tiles every block of the
+// rescan adds up the sums before its own itself, which saves the launch between; up to
+// kSmallScan items one block does it all in one launch.
 //
 // Radix sort: 8-bit digits over the bits in use, one pass per digit, each pass three launches:
 //   histogram  - a block counts the digits of its tile in LDS and writes them digit-major
@@ -16,6 +18,7 @@
 //                digit in LDS; per-digit prefixes over the waves and over the digits place
 //                every key in an LDS copy of the tile sorted by digit, from which consecutive
 //                threads write each digit's run to consecutive output positions.
+// Up to kSmallSort pairs one block keeps the pairs in LDS and does every pass in one launch.
 // Within a wave the LDS read of a digit's running count and the group leader's write of the
 // new count are issued in program order, so every lane of the group sees the count before it.
 //
@@ -42,6 +45,9 @@ constexpr int kSortItems = 8;                       // radix tile: 2048 keys
 constexpr int64_t kSortTile = (int64_t)kThreads * kSortItems;
 constexpr int kDigitBits = 8;
 constexpr int kDigits = 1 << kDigitBits;
+constexpr int kSmallScan = 16 << 10;                // items one block scans
+constexpr int kFoldSums = 1024;                     // tiles whose sums every block adds up itself
+constexpr int kSmallSort = 8 << 10;                 // pairs one block sorts: 144 of 160 KB LDS
 constexpr int kMaxBlockSums = 1 << 20;              // tile sums scanned by one block: 2^31 items
 static_assert(kThreads == kDigits, "the scatter kernel gives each thread one digit");
 
@@ -127,7 +133,8 @@ __global__ __launch_bounds__(1024) void k_scan_sums(int64_t *sums, int64_t nb) {
   }
 }
 
-template <class T>
+// kFold: sums holds the tile sums, else their exclusive prefixes.
+template <class T, bool kFold>
 __global__ __launch_bounds__(kThreads) void k_scan_apply(const T *in, int64_t *out, int64_t n,
                                                          const int64_t *sums) {
   __shared__ int64_t sh[kWaves];
@@ -138,9 +145,44 @@ __global__ __launch_bounds__(kThreads) void k_scan_apply(const T *in, int64_t *o
     v[i] = base + i < n ? (int64_t)in[base + i] : 0;
     s += v[i];
   }
-  int64_t run = sums[blockIdx.x] + block_excl_sum(s, sh, nullptr);
+  int64_t run = 0;
+  if (kFold) {
+    int64_t part = 0;
+    for (int i = threadIdx.x; i < (int)blockIdx.x; i += kThreads) part += sums[i];
+    block_excl_sum(part, sh, &run);
+  } else {
+    run = sums[blockIdx.x];
+  }
+  run += block_excl_sum(s, sh, nullptr);
   for (int i = 0; i < kScanItems; i++) {
     if (base + i < n) out[base + i] = run;
+    run += v[i];
+  }
+}
+
+// The whole scan in one block: every thread takes consecutive items.  Three launches of a few
+// microseconds each are what a short scan costs otherwise.
+template <class T>
+__global__ __launch_bounds__(1024) void k_scan_small(const T *in, int64_t *out, int n) {
+  __shared__ int64_t sh[16];
+  constexpr int kMost = kSmallScan / 1024;
+  const int per = (n + 1023) / 1024, lo = threadIdx.x * per;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int64_t v[kMost];
+  int64_t s = 0;
+#pragma unroll
+  for (int i = 0; i < kMost; i++) {
+    v[i] = i < per && lo + i < n ? (int64_t)in[lo + i] : 0;
+    s += v[i];
+  }
+  const int64_t inc = wave_incl_sum(s);
+  if (lane == 63) sh[w] = inc;
+  __syncthreads();   // in may be out: everything has been read
+  int64_t run = inc - s;
+  for (int i = 0; i < w; i++) run += sh[i];
+#pragma unroll
+  for (int i = 0; i < kMost; i++) {
+    if (i < per && lo + i < n) out[lo + i] = run;
     run += v[i];
   }
 }
@@ -154,12 +196,20 @@ size_t scan_temp(int64_t n) {
 template <class T>
 hipError_t scan_run(const T *in, int64_t *out, int64_t n, hipStream_t st, Carve &tmp) {
   if (n <= 0) return hipSuccess;
+  if (n <= kSmallScan) {
+    k_scan_small<T><<<1, 1024, 0, st>>>(in, out, (int)n);
+    return hipGetLastError();
+  }
   const unsigned nb = grid_for(n, kScanTile);
   if (nb > kMaxBlockSums) return hipErrorInvalidValue;
   int64_t *sums = tmp.take<int64_t>(nb);
   k_scan_tiles<T><<<nb, kThreads, 0, st>>>(in, n, sums);
-  k_scan_sums<<<1, 1024, 0, st>>>(sums, nb);
-  k_scan_apply<T><<<nb, kThreads, 0, st>>>(in, out, n, sums);
+  if (nb <= kFoldSums) {
+    k_scan_apply<T, true><<<nb, kThreads, 0, st>>>(in, out, n, sums);
+  } else {
+    k_scan_sums<<<1, 1024, 0, st>>>(sums, nb);
+    k_scan_apply<T, false><<<nb, kThreads, 0, st>>>(in, out, n, sums);
+  }
   return hipGetLastError();
 }
 
@@ -261,6 +311,88 @@ __global__ __launch_bounds__(kThreads) void k_rs_scatter(const K *kin, const V *
   }
 }
 
+// All passes in one block: the pairs live in registers (wave w holds the w-th part of them, in
+// rounds of 64) and are ranked as in k_rs_scatter; between passes they go through LDS, where a
+// digit's run starts at the prefix over digits and waves.
+template <class K, class V>
+__global__ __launch_bounds__(1024) void k_sort_small(const K *kin, const V *vin, K *kout, V *vout,
+                                                     int n, int passes) {
+  constexpr int kW = 16, kMost = kSmallSort / 1024;
+  __shared__ K sk[kSmallSort];
+  __shared__ V sv[kSmallSort];
+  __shared__ uint32_t wcnt[kW][kDigits];   // running counts, then first slots
+  __shared__ uint32_t wsum[kDigits / 64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int rounds = (n + 1023) / 1024, base = w * 64 * rounds + lane;
+  const uint64_t below = (1ull << lane) - 1;
+  K kk[kMost];
+  V vv[kMost];
+  uint32_t rk[kMost];
+#pragma unroll
+  for (int r = 0; r < kMost; r++) {
+    const int j = base + 64 * r;
+    const bool live = r < rounds && j < n;
+    kk[r] = live ? kin[j] : K(0);
+    vv[r] = live ? vin[j] : V(0);
+  }
+  for (int ps = 0, bit = 0; ps < passes; ps++, bit += kDigitBits) {
+    for (int i = threadIdx.x; i < kW * kDigits; i += 1024) (&wcnt[0][0])[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kMost; r++) {
+      if (r >= rounds) break;
+      const bool live = base + 64 * r < n;
+      const uint32_t d = digit_of(kk[r], bit);
+      uint64_t peers = __ballot(live);
+      for (int b = 0; b < kDigitBits; b++) {
+        const uint64_t ones = __ballot(live && ((d >> b) & 1u));
+        peers &= ((d >> b) & 1u) ? ones : ~ones;
+      }
+      const uint32_t before = wcnt[w][d];          // every lane of the group reads first
+      rk[r] = before + (uint32_t)__popcll(peers & below);
+      if (live && (peers & below) == 0) wcnt[w][d] = before + (uint32_t)__popcll(peers);
+    }
+    __syncthreads();
+    uint32_t cnt = 0, start = 0;
+    if (threadIdx.x < kDigits) {   // whole waves: a digit per thread
+      for (int i = 0; i < kW; i++) {
+        const uint32_t c = wcnt[i][threadIdx.x];
+        wcnt[i][threadIdx.x] = cnt;
+        cnt += c;
+      }
+      const uint32_t inc = (uint32_t)wave_incl_sum((int64_t)cnt);
+      start = inc - cnt;
+      if (lane == 63) wsum[w] = inc;
+    }
+    __syncthreads();
+    if (threadIdx.x < kDigits) {
+      for (int i = 0; i < w; i++) start += wsum[i];
+      for (int i = 0; i < kW; i++) wcnt[i][threadIdx.x] += start;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kMost; r++) {
+      if (r >= rounds || base + 64 * r >= n) break;
+      const uint32_t slot = wcnt[w][digit_of(kk[r], bit)] + rk[r];
+      sk[slot] = kk[r];
+      sv[slot] = vv[r];
+    }
+    __syncthreads();
+    if (ps + 1 == passes) break;
+#pragma unroll
+    for (int r = 0; r < kMost; r++) {
+      const int j = base + 64 * r;
+      if (r >= rounds || j >= n) break;
+      kk[r] = sk[j];
+      vv[r] = sv[j];
+    }
+  }
+  for (int j = threadIdx.x; j < n; j += 1024) {
+    kout[j] = sk[j];
+    vout[j] = sv[j];
+  }
+}
+
 template <class K, class V>
 hipError_t radix_sort(const K *kin, K *kout, const V *vin, V *vout, int64_t n, int end_bit,
                       hipStream_t st, TempAlloc ta) {
@@ -271,6 +403,10 @@ hipError_t radix_sort(const K *kin, K *kout, const V *vin, V *vout, int64_t n, i
     hipError_t e = hipMemcpyAsync(kout, kin, sizeof(K) * n, hipMemcpyDeviceToDevice, st);
     if (e != hipSuccess) return e;
     return hipMemcpyAsync(vout, vin, sizeof(V) * n, hipMemcpyDeviceToDevice, st);
+  }
+  if (n <= kSmallSort) {
+    k_sort_small<K, V><<<1, 1024, 0, st>>>(kin, vin, kout, vout, (int)n, passes);
+    return hipGetLastError();
   }
   const int64_t nb = grid_for(n, kSortTile);
   const int64_t nc = nb * kDigits;

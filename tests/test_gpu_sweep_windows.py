@@ -131,3 +131,23 @@ def test_common_denominators_match_oracle(weight):
             assert np.array_equal(r["q_components"], oc), (extra, omega)
             for k in STAT_KEYS:
                 assert r[k] == ost[k], (extra, omega, k)
+
+
+@pytest.mark.parametrize("n", [1, 2, 1023, 1024, 1025, 8191, 8192, 8193, 16383, 16384, 16385])
+def test_sort_and_scan_sizes_match_oracle(n):
+    """Levels of as many units, and entries, as one block sorts or scans, one fewer and one more."""
+    from paper_2608_03695_amd import mslm
+    rng = np.random.default_rng(n)
+    ring = [(i, (i + 1) % n) for i in range(n)] if n > 2 else []
+    far = rng.integers(0, n, (n // 2, 2))
+    more = sorted({(min(a, b), max(a, b)) for a, b in far.tolist() if abs(a - b) > 2
+                   and abs(a - b) < n - 2})
+    tg = gen.from_edge_lists(n, [ring + more] if n > 2 else [[(0, 1)] * (n - 1)], name="ring")
+    om, oc, ost = oracle.OracleGraph(tg, 1).leiden(1, max_levels=32, max_iterations=2, seed=2)
+    g = mslm.Graph(tg, 1)
+    m, r = g.leiden(1, seed=2)
+    g.close()
+    assert np.array_equal(m, om)
+    assert np.array_equal(r["q_components"], oc)
+    for k in STAT_KEYS:
+        assert r[k] == ost[k], k
