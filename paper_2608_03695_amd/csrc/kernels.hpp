@@ -2187,18 +2187,18 @@ __device__ inline void pos_row(const View0 &g, const SolveDev &sd, int64_t v, in
   }
 }
 
-// rows of at most 32 entries one thread each; longer rows are listed for a wave each
-__global__ void k_pos_rows(View0 g, SolveDev sd, const int32_t *units, int64_t n,
+// Rows of at most 32 entries take kPosGroup lanes each, whose reads and writes of the row are
+// consecutive (one thread each: 2.5 ms for 27.6M entries); longer rows are listed for a wave each.
+constexpr int kPosGroup = 8;
+__global__ __launch_bounds__(256) void k_pos_rows(View0 g, SolveDev sd, const int32_t *units, int64_t n,
                            const int64_t *prp, const int32_t *pos, int32_t *pcol, int32_t *pw,
                            int32_t *wide, uint32_t *nwide, PosLabels pl) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int64_t v = units[i];
-  if (g.degree(v) > 32) {
-    wide[atomicAdd(nwide, 1u)] = (int32_t)i;
-    return;
-  }
-  pos_row(g, sd, v, prp[i], pos, pcol, pw, 0, 1, pl);
+  const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kPosGroup;
+  const int gl = threadIdx.x % kPosGroup;
+  const int64_t v = i < n ? units[i] : 0;
+  const bool is_long = i < n && g.degree(v) > 32;
+  wave_append(wide, nwide, is_long && gl == 0, (int32_t)i);
+  if (i < n && !is_long) pos_row(g, sd, v, prp[i], pos, pcol, pw, gl, kPosGroup, pl);
 }
 
 __global__ void k_pos_rows_wide(View0 g, SolveDev sd, const int32_t *units, const int64_t *prp,
@@ -3239,7 +3239,10 @@ __device__ inline bool ref_beaten(const V &g, const SolveDev &sd, int64_t v, con
     if (comm[x] != D || propr[x] != stamp) continue;
     if (g.wt(row, e, x) == 0) continue;
     uint64_t hx = priority(sm, it, lvl, 1, (uint32_t)(x - off));
-    if (outranks(hx, (uint32_t)x, hv, (uint32_t)v)) beaten = true;
+    if (outranks(hx, (uint32_t)x, hv, (uint32_t)v)) {
+      beaten = true;
+      break;
+    }
   }
   return beaten;
 }
@@ -3589,29 +3592,83 @@ __device__ inline void uf_unite(int32_t *parent, int32_t a, int32_t b) {
   }
 }
 
-__global__ void k_uf_init(int32_t *parent, const int64_t *lo, const int64_t *hi, int nr) {
+// body(v, first, step) for every element v of the ranges: by 16 lanes, or by the whole wave for
+// rows of more than 1024 entries.
+template <class F>
+__device__ inline void uf_rows(const View0 &g, const int64_t *lo, const int64_t *hi, int nr,
+                               F body) {
+  const int lane = threadIdx.x & 63;
+  const int64_t wid = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
+  for (int k = 0; k < nr; k++)
+    for (int64_t v0 = lo[k] + 4 * wid; v0 < hi[k]; v0 += 4 * nw) {
+      const int64_t v = v0 + lane / 16;
+      const bool live = v < hi[k];
+      const bool is_long = live && g.degree(v) > 1024;
+      if (live && !is_long) body(v, lane & 15, 16);
+      for (uint64_t m = __ballot(is_long && (lane & 15) == 0); m; m &= m - 1)
+        body(v0 + __builtin_ctzll(m) / 16, lane, 64);
+    }
+}
+
+// First every element hooks onto its smallest neighbour of the same label (a smaller one, so no
+// cycles and no atomics); then, flattened, every tree hooks onto the smallest root next to it
+// (kRoots), which leaves few trees, and nearly every edge of k_uf_link finds its ends under one root
+// by one load each.  Linking from single elements had all edges of a community fight over its
+// root (500k elements in 12 communities 2.75 ms), from trees of the first round too (5.0 ms).
+template <bool kRoots>
+__global__ __launch_bounds__(256) void k_uf_hook(View0 g, SolveDev sd, const int64_t *lo,
+                                                 const int64_t *hi, int nr, const uint32_t *lab,
+                                                 int32_t *parent) {
+  auto at = [&](int64_t x) {
+    return __hip_atomic_load(parent + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  uf_rows(g, lo, hi, nr, [&](int64_t v, int first, int step) {
+    View0::Row row = g.row(v, sd);
+    const uint32_t L = lab[v];
+    const int32_t own = kRoots ? at(v) : (int32_t)v;
+    int32_t best = own;
+    for (int64_t e = row.lo + first; e < row.hi; e += step) {
+      const int32_t x = g.col[e];
+      if (lab[x] != L) continue;
+      const int32_t r = kRoots ? at(x) : x;
+      if (r < best && g.wt(row, e, x) != 0) best = r;
+    }
+    for (int m = step / 2; m >= 1; m >>= 1) {
+      const int32_t o = __shfl_xor(best, m, 64);
+      best = o < best ? o : best;
+    }
+    if (first != 0) return;
+    if (!kRoots) parent[v] = best;
+    else if (best < own && best < at(own)) atomicMin(parent + own, best);
+  });
+}
+
+__global__ __launch_bounds__(256) void k_uf_flatten(int32_t *parent, const int64_t *lo,
+                                                    const int64_t *hi, int nr) {
   int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int k = 0; k < nr; k++)
-    for (int64_t i = lo[k] + tid; i < hi[k]; i += stride) parent[i] = (int32_t)i;
+    for (int64_t i = lo[k] + tid; i < hi[k]; i += stride) {
+      const int32_t r = uf_find(parent, (int32_t)i);
+      __hip_atomic_store(parent + i, r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
 }
 
 __global__ __launch_bounds__(256) void k_uf_link(View0 g, SolveDev sd, const int64_t *lo,
                                                  const int64_t *hi, int nr, const uint32_t *lab,
                                                  int32_t *parent) {
-  const int lane = threadIdx.x & 63;
-  int64_t wid = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
-  for (int k = 0; k < nr; k++)
-    for (int64_t v = lo[k] + wid; v < hi[k]; v += nw) {
-      View0::Row row = g.row(v, sd);
-      const uint32_t L = lab[v];
-      for (int64_t e = row.lo + lane; e < row.hi; e += 64) {
-        int32_t x = g.col[e];
-        if (x <= v || lab[x] != L || g.wt(row, e, x) == 0) continue;
-        uf_unite(parent, (int32_t)v, x);
-      }
+  uf_rows(g, lo, hi, nr, [&](int64_t v, int first, int step) {
+    View0::Row row = g.row(v, sd);
+    const uint32_t L = lab[v];
+    const int32_t rv = __hip_atomic_load(parent + v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int64_t e = row.lo + first; e < row.hi; e += step) {
+      const int32_t x = g.col[e];
+      if (x <= v || lab[x] != L || g.wt(row, e, x) == 0) continue;
+      if (__hip_atomic_load(parent + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == rv) continue;
+      uf_unite(parent, (int32_t)v, x);
     }
+  });
 }
 
 // Root of every element into a separate array: other threads' path halving keeps rewriting
@@ -3680,13 +3737,39 @@ __global__ void k_q_w(View0 g, int64_t n, const int32_t *memb, int64_t *W) {
 }
 
 // Sigma of a membership: per Sigma slice and label, the sum of the null-model degrees
-__global__ void k_sigma_build_memb(View0 g, int64_t n, const int32_t *memb, SliceTable t) {
-  int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= n) return;
-  int gs;
-  int64_t k;
-  g.pent(v, 0, gs, k);
-  if (k > 0) tab_add(t, gs, (uint32_t)memb[v], (int32_t)k, false);
+// (a block's kMembUnits units are added up in LDS first: final memberships have few labels, and
+// 500k units of 12 communities and one slice took 2.0 ms of atomics on 12 words; a label that
+// finds no slot in kMembProbes goes to the table itself).
+constexpr int kMembUnits = 4096, kMembLg = 10, kMembProbes = 4;
+__global__ __launch_bounds__(256) void k_sigma_build_memb(View0 g, int64_t n, const int32_t *memb,
+                                                          SliceTable t) {
+  __shared__ unsigned long long sk[1 << kMembLg];   // slice << 32 | label, ~0: free
+  __shared__ int32_t sv[1 << kMembLg];
+  for (int i = threadIdx.x; i < 1 << kMembLg; i += 256) {
+    sk[i] = ~0ull;
+    sv[i] = 0;
+  }
+  __syncthreads();
+  const int64_t v0 = (int64_t)blockIdx.x * kMembUnits;
+  for (int64_t v = v0 + threadIdx.x; v < v0 + kMembUnits && v < n; v += 256) {
+    int gs;
+    int64_t k;
+    g.pent(v, 0, gs, k);
+    if (k <= 0) continue;
+    const uint32_t lab = (uint32_t)memb[v];
+    const unsigned long long key = (unsigned long long)(uint32_t)gs << 32 | lab;
+    uint32_t h = (lab * 0x9e3779b1u + (uint32_t)gs * 0x85ebca6bu) >> (32 - kMembLg);
+    int p = 0;
+    for (; p < kMembProbes; p++, h = (h + 1) & ((1u << kMembLg) - 1)) {
+      const unsigned long long was = atomicCAS(sk + h, ~0ull, key);
+      if (was == ~0ull || was == key) break;
+    }
+    if (p < kMembProbes) atomicAdd(sv + h, (int32_t)k);
+    else tab_add(t, gs, lab, (int32_t)k, false);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < 1 << kMembLg; i += 256)
+    if (sk[i] != ~0ull) tab_add(t, (int)(sk[i] >> 32), (uint32_t)sk[i], sv[i], false);
 }
 
 // Scaled supra-degree of every unit of one solve under the global null model:

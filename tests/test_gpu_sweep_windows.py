@@ -151,3 +151,20 @@ def test_sort_and_scan_sizes_match_oracle(n):
     assert np.array_equal(r["q_components"], oc)
     for k in STAT_KEYS:
         assert r[k] == ost[k], k
+
+
+@pytest.mark.parametrize("gamma", [F(1, 4), F(40)], ids=["few", "many"])
+def test_final_labels_match_oracle(gamma):
+    """Final memberships of a handful of labels and of more than a block's label table holds, and
+    communities that come apart into many trees of short and long rows."""
+    from paper_2608_03695_amd import mslm
+    tg = _hubs((1500, 5200))
+    om, oc, ost = oracle.OracleGraph(tg, 1).leiden(gamma, max_levels=32, max_iterations=2, seed=4)
+    g = mslm.Graph(tg, 1)
+    m, r = g.leiden(gamma, seed=4)
+    g.close()
+    assert (r["n_communities"] > 1024) == (gamma == 40)
+    assert np.array_equal(m, om)
+    assert np.array_equal(r["q_components"], oc)
+    for k in STAT_KEYS:
+        assert r[k] == ost[k], k
