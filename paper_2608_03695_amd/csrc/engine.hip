@@ -167,7 +167,7 @@ __global__ void k_build_validate(const int32_t *src, const int32_t *dst, const i
 // every intra edge in both directions, keyed (row, col); the slice comes from the offsets
 __global__ void k_build_intra(const int32_t *src, const int32_t *dst, const int32_t *w,
                               const int64_t *off, int32_t T, int32_t N, int64_t E, int shift,
-                              uint64_t *keys, int64_t *vals) {
+                              uint64_t *keys, int32_t *vals) {
   int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= E) return;
   int lo = 0, hi = T;   // off[lo] <= e < off[hi]
@@ -177,7 +177,7 @@ __global__ void k_build_intra(const int32_t *src, const int32_t *dst, const int3
   }
   int64_t base = (int64_t)lo * N;
   uint64_t u = (uint64_t)(base + src[e]), x = (uint64_t)(base + dst[e]);
-  int64_t ww = w ? w[e] : 1;
+  const int32_t ww = w ? w[e] : 1;
   keys[2 * e] = (u << shift) | x;
   vals[2 * e] = ww;
   keys[2 * e + 1] = (x << shift) | u;
@@ -204,12 +204,12 @@ __global__ void k_mark_present(const int32_t *src, const int32_t *dst, const int
 // last and is dropped
 __global__ void k_build_inter(int32_t N, int64_t P, const int32_t *ps, const int32_t *pr,
                               const int32_t *pc, const uint8_t *present, int shift,
-                              uint64_t *keys, int64_t *vals) {
+                              uint64_t *keys, int32_t *vals) {
   int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= (int64_t)N * P) return;
   const int64_t p = t / N, i = t - p * N;
   uint64_t v = (uint64_t)((int64_t)ps[p] * N + i), x = (uint64_t)((int64_t)pr[p] * N + i);
-  int64_t c = pc[p];
+  int32_t c = pc[p];
   if (present && !(present[v] && present[x])) {
     v = x = (1ull << shift) - 1;
     c = 0;
@@ -236,16 +236,34 @@ __global__ void k_coupling_total(const int64_t *rp, const int32_t *col, const in
   if ((threadIdx.x & 63) == 0 && t) atomicAdd(out, t);
 }
 
-__global__ void k_build_csr(const uint64_t *keys, const int64_t *vals, int64_t m, int shift,
-                            int32_t *col, int32_t *w, int64_t *rowcnt, int *nonunit) {
+// Columns and weights of the sorted unique entries; nonunit: a weight other than 1 is there (one
+// look per wave, and no atomic once it is known: an atomic per entry and one per row count took
+// 5.1 ms for 28M entries, this and k_build_rows together 0.4).
+__global__ void k_build_csr(const uint64_t *keys, const int32_t *vals, int64_t m, int shift,
+                            int32_t *col, int32_t *w, int *nonunit) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= m) return;
-  uint64_t k = keys[i];
-  col[i] = (int32_t)(k & ((1ull << shift) - 1));
-  int64_t v = vals[i];
-  w[i] = (int32_t)v;
-  if (v > 1) atomicOr(nonunit, 1);
-  atomicAdd(reinterpret_cast<unsigned long long *>(rowcnt + (k >> shift)), 1ull);
+  int32_t v = 1;
+  if (i < m) {
+    col[i] = (int32_t)(keys[i] & ((1ull << shift) - 1));
+    v = vals[i];
+    w[i] = v;
+  }
+  if (__any(v != 1) && (threadIdx.x & 63) == 0 &&
+      __hip_atomic_load(nonunit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
+    atomicOr(nonunit, 1);
+}
+
+// Row starts: the first entry of row v or a later one, by binary search in the sorted keys.
+__global__ void k_build_rows(const uint64_t *keys, int64_t m, int shift, int64_t n, int64_t *rp) {
+  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (v > n) return;
+  int64_t lo = 0, hi = m;
+  while (lo < hi) {
+    const int64_t mid = (lo + hi) >> 1;
+    if ((int64_t)(keys[mid] >> shift) < v) lo = mid + 1;
+    else hi = mid;
+  }
+  rp[v] = lo;
 }
 
 // Reverse entries: entry e = (u, x) (its sorted unique key) finds (x, u) in x's row, whose
@@ -362,7 +380,7 @@ void build_graph(GraphDev &g, const mslm_graph_desc &d, hipStream_t st, Workspac
   // keys (row << b) | column with b the bits of n: the sort covers the bits in use
   const int shift = bits_for((uint64_t)n);
   uint64_t *k1 = ws->akeys.get<uint64_t>(mraw);
-  int64_t *v1 = ws->avals.get<int64_t>(mraw);
+  int32_t *v1 = ws->avals.get<int32_t>(mraw);
   if (E > 0) k_build_intra<<<nblk(E), kBS, 0, st>>>(src, dst, w, off, T, N, E, shift, k1, v1);
   if (ninter > 0) {
     int32_t *dp = ws->b_pairs.get<int32_t>(3 * P);
@@ -379,10 +397,10 @@ void build_graph(GraphDev &g, const mslm_graph_desc &d, hipStream_t st, Workspac
                                                 k1 + 2 * E, v1 + 2 * E);
   }
   uint64_t *k2 = ws->akeys2.get<uint64_t>(mraw);
-  int64_t *v2 = ws->avals2.get<int64_t>(mraw);
-  MSLM_PRIM(sort_pairs_u64_i64(k1, k2, v1, v2, mraw, 2 * shift, st, temp_alloc(ws)));
+  int32_t *v2 = ws->avals2.get<int32_t>(mraw);
+  MSLM_PRIM(sort_pairs_u64_i32(k1, k2, v1, v2, mraw, 2 * shift, st, temp_alloc(ws)));
   int64_t *dn = ws->nuniq.get<int64_t>(1);
-  MSLM_PRIM(reduce_by_key_u64_i64(k2, k1, v2, v1, dn, mraw, st, temp_alloc(ws)));
+  MSLM_PRIM(reduce_by_key_u64_i32(k2, k1, v2, v1, dn, mraw, st, temp_alloc(ws)));
   int64_t m = 0;
   d2h(&m, dn, 1, st);
   MSLM_HIP(hipStreamSynchronize(st));
@@ -396,13 +414,11 @@ void build_graph(GraphDev &g, const mslm_graph_desc &d, hipStream_t st, Workspac
   g.nnz = m;
   int32_t *col = g.col.get<int32_t>(m);
   int32_t *wv = g.w.get<int32_t>(m);
-  int64_t *cnt = ws->rowcnt.get<int64_t>(n + 1);
   int *flags = ws->flag.get<int>(2);
-  MSLM_HIP(hipMemsetAsync(cnt, 0, sizeof(int64_t) * (n + 1), st));
   MSLM_HIP(hipMemsetAsync(flags, 0, sizeof(int) * 2, st));
-  if (m > 0) k_build_csr<<<nblk(m), kBS, 0, st>>>(k1, v1, m, shift, col, wv, cnt, flags);
+  if (m > 0) k_build_csr<<<nblk(m), kBS, 0, st>>>(k1, v1, m, shift, col, wv, flags);
   int64_t *rp = g.rp.get<int64_t>(n + 1);
-  MSLM_PRIM(exclusive_sum_i64(cnt, rp, n + 1, st, temp_alloc(ws)));
+  k_build_rows<<<nblk(n + 1), kBS, 0, st>>>(k1, m, shift, n, rp);
   int32_t *rev = g.rev.get<int32_t>(m);
   if (m > 0) k_build_rev<<<nblk(m), kBS, 0, st>>>(k1, m, shift, rp, col, rev);
   int32_t *kd = g.k.get<int32_t>(n);
