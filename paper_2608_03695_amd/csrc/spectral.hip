@@ -32,7 +32,7 @@ namespace {
 constexpr int kSB = 256;          // threads per block
 constexpr int kDotBlocks = 512;   // fixed grid of the reductions
 constexpr int kMdotBlocks = 1024; // row ranges of the reorthogonalisation dot products
-constexpr int kMdotVec = 4;       // vectors per block (a timing sweep of 4/8/16)
+constexpr int kMdotVec = 8;       // vectors per block: a solve of 50k x 8 takes 59.2 / 58.3 / 62.5 ms at 4/8/16
 constexpr int kMaxK = 32;         // eigenvectors / clusters
 constexpr int kMaxSteps = 256;    // Krylov dimension
 constexpr int kFixShift = 40;     // fixed-point scale of the k-means sums
@@ -158,8 +158,8 @@ __global__ void k_lanczos_sub(double *w, const double *vj, const double *vp, dou
 
 // partial[b * stride + i] = block b's share of V_i . w for i < cnt and, with norm, of w . w at
 // i = cnt (stride = cnt + norm; V column-major, n per vector).  Block (b, y) takes the
-// contiguous row range b and the four vectors 4y..4y+3 (a grid of kMdotBlocks x
-// ceil(stride / 4) blocks): many short blocks keep enough loads in flight.
+// contiguous row range b and kMdotVec vectors from kMdotVec*y on (a grid of kMdotBlocks x
+// ceil(stride / kMdotVec) blocks): many short blocks keep enough loads in flight.
 __global__ __launch_bounds__(kSB) void k_mdot_partial(const double *V, int cnt, const double *w,
                                                      int64_t n, int norm, const int *gate,
                                                      double *partial) {
@@ -173,14 +173,26 @@ __global__ __launch_bounds__(kSB) void k_mdot_partial(const double *V, int cnt, 
   double s[kMdotVec];
 #pragma unroll
   for (int u = 0; u < kMdotVec; u++) s[u] = 0.0;
+  // whole groups: no branch between the loads (with one, and with one vector at a time in k_msub,
+  // the two took 23 of a solve's 65 ms)
+  if (i0 + kMdotVec <= cnt) {
+    const double *v0 = V + (int64_t)i0 * n;
 #pragma unroll 4
-  for (int64_t k = lo + threadIdx.x; k < hi; k += blockDim.x) {
-    const double wk = w[k];
+    for (int64_t k = lo + threadIdx.x; k < hi; k += kSB) {
+      const double wk = w[k];
 #pragma unroll
-    for (int u = 0; u < kMdotVec; u++) {
-      const int i = i0 + u;
-      if (i < cnt) s[u] += V[(int64_t)i * n + k] * wk;
-      else if (i == cnt && norm) s[u] += wk * wk;
+      for (int u = 0; u < kMdotVec; u++) s[u] += v0[(int64_t)u * n + k] * wk;
+    }
+  } else {
+#pragma unroll 4
+    for (int64_t k = lo + threadIdx.x; k < hi; k += kSB) {
+      const double wk = w[k];
+#pragma unroll
+      for (int u = 0; u < kMdotVec; u++) {
+        const int i = i0 + u;
+        if (i < cnt) s[u] += V[(int64_t)i * n + k] * wk;
+        else if (i == cnt && norm) s[u] += wk * wk;
+      }
     }
   }
   // the block's sums: wave shuffles, then the four waves in index order
@@ -199,13 +211,22 @@ __global__ __launch_bounds__(kSB) void k_mdot_partial(const double *V, int cnt, 
 }
 
 // w -= V h (cnt vectors); gate as for k_mdot_partial
+constexpr int kMsubVec = 8;
 __global__ void k_msub(const double *V, int cnt, const double *h, const int *gate, double *w,
                        int64_t n) {
   if (gate && *gate == 0) return;
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= n) return;
   double s = 0.0;
-  for (int i = 0; i < cnt; i++) s += V[(int64_t)i * n + k] * h[i];
+  int i = 0;
+  for (; i + kMsubVec <= cnt; i += kMsubVec) {   // loads in flight together, summed in order
+    double v[kMsubVec];
+#pragma unroll
+    for (int u = 0; u < kMsubVec; u++) v[u] = V[(int64_t)(i + u) * n + k];
+#pragma unroll
+    for (int u = 0; u < kMsubVec; u++) s += v[u] * h[i + u];
+  }
+  for (; i < cnt; i++) s += V[(int64_t)i * n + k] * h[i];
   w[k] -= s;
 }
 
