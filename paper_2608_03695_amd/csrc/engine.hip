@@ -286,11 +286,36 @@ __global__ void k_build_rev(const uint64_t *keys, int64_t m, int shift, const in
   rev[e] = (int32_t)(lo - r0);
 }
 
-// Intra degree of every unit and, per slice, 2m_s and the count of units with nonzero degree.
+// 2m_s of every slice: twice the weight of its edges as listed, in 64 bits.  The sums of repeated
+// pairs are kept in 32 bits through the sort; these totals say whether any of them could have
+// left that range, which the sums themselves no longer show.  A block takes kTotalEdges edges,
+// nearly always of one slice.
+constexpr int64_t kTotalEdges = 4096;
+__global__ __launch_bounds__(256) void k_build_totals(const int32_t *w, const int64_t *off,
+                                                      int32_t T, int64_t E, int64_t *twom) {
+  const int64_t b0 = (int64_t)blockIdx.x * kTotalEdges;
+  const int64_t b1 = b0 + kTotalEdges < E ? b0 + kTotalEdges : E;
+  int lo = 0, hi = T;   // off[lo] <= b0 < off[hi]
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (off[mid] <= b0) lo = mid;
+    else hi = mid;
+  }
+  for (int s = lo; s < T && off[s] < b1; s++) {
+    const int64_t e0 = off[s] > b0 ? off[s] : b0, e1 = off[s + 1] < b1 ? off[s + 1] : b1;
+    int64_t sum = 0;
+    for (int64_t e = e0 + threadIdx.x; e < e1; e += blockDim.x) sum += w[e];
+    sum = wave_sum64(sum);
+    if ((threadIdx.x & 63) == 0 && sum)
+      atomicAdd(reinterpret_cast<unsigned long long *>(twom + s), (unsigned long long)(2 * sum));
+  }
+}
+
+// Intra degree of every unit and, per slice, the count of units with nonzero degree.
 // A wave's units are consecutive, so they nearly always lie in one slice: the wave sums first
 // and issues one atomic per counter (one atomic per unit on 64 addresses serialises).
 __global__ void k_build_degree(const int64_t *rp, const int32_t *col, const int32_t *w, int64_t n,
-                               int32_t N, int32_t *kdeg, int64_t *twom, int64_t *nz) {
+                               int32_t N, int32_t *kdeg, int64_t *nz) {
   const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const bool live = v < n;
   const int64_t s = live ? v / N : -1;
@@ -306,17 +331,10 @@ __global__ void k_build_degree(const int64_t *rp, const int32_t *col, const int3
   // lane 0 holds the wave's smallest unit, so it is live whenever any lane is
   const int64_t s0 = __shfl(s, 0, 64);
   if (__all(!live || s == s0)) {
-    int64_t dd = d, z = d != 0;
-    for (int m = 32; m >= 1; m >>= 1) {
-      dd += shfl_xor64(dd, m);
-      z += shfl_xor64(z, m);
-    }
-    if ((threadIdx.x & 63) == 0 && dd) {
-      atomicAdd(reinterpret_cast<unsigned long long *>(twom + s0), (unsigned long long)dd);
-      atomicAdd(reinterpret_cast<unsigned long long *>(nz + s0), (unsigned long long)z);
-    }
+    const uint64_t z = __ballot(d != 0);
+    if ((threadIdx.x & 63) == 0 && z)
+      atomicAdd(reinterpret_cast<unsigned long long *>(nz + s0), (unsigned long long)__popcll(z));
   } else if (d) {
-    atomicAdd(reinterpret_cast<unsigned long long *>(twom + s), (unsigned long long)d);
     atomicAdd(reinterpret_cast<unsigned long long *>(nz + s), 1ull);
   }
 }
@@ -424,7 +442,8 @@ void build_graph(GraphDev &g, const mslm_graph_desc &d, hipStream_t st, Workspac
   int32_t *kd = g.k.get<int32_t>(n);
   int64_t *twom = ws->b_twom.get<int64_t>(2 * T);
   MSLM_HIP(hipMemsetAsync(twom, 0, sizeof(int64_t) * 2 * T, st));
-  k_build_degree<<<nblk(n), kBS, 0, st>>>(rp, col, wv, n, N, kd, twom, twom + T);
+  if (w && E > 0) k_build_totals<<<nblk(E, kTotalEdges), 256, 0, st>>>(w, off, T, E, twom);
+  k_build_degree<<<nblk(n), kBS, 0, st>>>(rp, col, wv, n, N, kd, twom + T);
   k_max_degree<<<nblk(n), kBS, 0, st>>>(rp, n, flags + 1);
   unsigned long long *ct = reinterpret_cast<unsigned long long *>(ws->nuniq.get<int64_t>(1));
   MSLM_HIP(hipMemsetAsync(ct, 0, sizeof(unsigned long long), st));
@@ -438,6 +457,8 @@ void build_graph(GraphDev &g, const mslm_graph_desc &d, hipStream_t st, Workspac
   MSLM_HIP(hipStreamSynchronize(st));
   g.ctot = (int64_t)hct;
   g.twom.assign(h.begin(), h.begin() + T);
+  if (!w)
+    for (int s = 0; s < T; s++) g.twom[s] = 2 * (d.slice_offsets[s + 1] - d.slice_offsets[s]);
   g.nzslice.assign(h.begin() + T, h.end());
   for (int s = 0; s < T; s++)
     if (g.twom[s] >= (int64_t)1 << 31)
