@@ -243,6 +243,7 @@ struct UnitCtx {
   int64_t k0;     // first profile degree
   int64_t p, q, pb, S0;
   double scale, lim;   // of the multi-slice estimates (SolveDev)
+  mutable bool tied = false;   // this lane met a near-tie that it could not settle
 };
 
 template <class V>
@@ -266,12 +267,14 @@ __device__ inline UnitCtx unit_ctx(const V &g, const SolveDev &sd, int64_t v, ui
 
 // Record how long unit v (decided `out`, one thread) stays at rest; kmax: its largest profile
 // degree when it spans several slices.  Rounded down by 2^-30, far above the rounding of the
-// doubles involved.
+// doubles involved.  tied: a comparison of the unit was left to the exact kernels, so its best
+// target may not be the best ("the heavier one" of a near-tie is no order: over several targets it
+// leads any number of steps down); such a unit is not at rest.
 __device__ inline void settle(const SolveDev &sd, const UnitCtx &u, uint32_t out, double slack,
-                              double kmax) {
+                              double kmax, bool tied) {
   if (!sd.rest) return;
   Rest r{-1, 0, 0};
-  if (out == kNone && slack >= 0.0) {
+  if (out == kNone && slack >= 0.0 && !tied) {
     const bool one = u.m <= 1;
     r.ctr = one ? (u.m ? u.gs0 : 0) : sd.nsl + u.j;
     const double den = 2.0 * (double)u.pb * (one ? (double)u.k0 : kmax);
@@ -331,7 +334,7 @@ struct Policy0 {
   }
   // how far staying is ahead of the best target (never above the true difference by more than
   // rounding, which settle() allows for)
-  __device__ static double slack(const UnitCtx &, const Score &stay, const Score &best, int64_t) {
+  __device__ static double slack(const UnitCtx &, const Score &stay, const Score &best) {
     return (double)(stay.g - best.g);
   }
   // the score of staying when the Sigma of the unit's own community is already known
@@ -406,7 +409,10 @@ __device__ inline int exact_cmp_flag(const V &g, const UnitCtx &u, const SolveDe
     g.pent(u.v, jj, gs, k);
     same = target_y(tab, gs, k, la, ka) == target_y(tab, gs, k, lb, kb);
   }
-  if (!same) atomicMin(sd.redo + u.j, sd.mark);
+  if (!same) {
+    atomicMin(sd.redo + u.j, sd.mark);
+    u.tied = true;
+  }
   return Wa > Wb ? 1 : (Wa < Wb ? -1 : 0);
 }
 
@@ -473,17 +479,9 @@ struct PolicyKT {
     else
       return exact_cmp_flag(g, u, sd, tab, a.lab, a.kind & 3, a.W, b.lab, b.kind & 3, b.W);
   }
-  // Without the exact path the best may be one of several targets too close to order.  Their
-  // weights are at most Wmax and their estimates at least about 0 (the empty community's), so each
-  // one's error is at most tie = (m + 8) 2^-49 q Wmax (1 + tiny), and a better one among them lies
-  // within 2 (best.er + tie) + tie of the best's estimate.  Wmax < 0: unknown.
-  __device__ static double slack(const UnitCtx &u, const Score &stay, const Score &best,
-                                 int64_t Wmax) {
+  __device__ static double slack(const UnitCtx &u, const Score &stay, const Score &best) {
     if (u.m <= 1) return (double)(stay.ex - best.ex);
-    const double d = ((stay.ap - stay.er) - (best.ap + best.er)) / u.scale;
-    if (Exact) return d;
-    if (Wmax < 0) return -1.0;
-    return d - best.er / u.scale - 4.0 * (double)(u.m + 8) * 0x1p-49 * (double)u.q * (double)Wmax;
+    return ((stay.ap - stay.er) - (best.ap + best.er)) / u.scale;
   }
   __device__ static bool prunable(const UnitCtx &u, int64_t W, const Score &best) {
     if (u.m <= 1) {
@@ -515,6 +513,11 @@ template <class P>
 struct IsMulti : std::false_type {};
 template <bool E>
 struct IsMulti<PolicyKT<E>> : std::true_type {};
+// policies whose near-ties are left to the exact kernels
+template <class P>
+struct LeavesTies : std::false_type {};
+template <>
+struct LeavesTies<PolicyKF> : std::true_type {};
 
 // Aggregated levels, units in at most one slice: the same int128 value as PolicyK's
 // single-slice case without the multi-slice machinery (far fewer registers).
@@ -542,7 +545,7 @@ struct PolicyK1 {
                             const Score &a, const Score &b) {
     return a.ex < b.ex ? -1 : (a.ex > b.ex ? 1 : 0);
   }
-  __device__ static double slack(const UnitCtx &, const Score &stay, const Score &best, int64_t) {
+  __device__ static double slack(const UnitCtx &, const Score &stay, const Score &best) {
     return (double)(stay.ex - best.ex);
   }
   __device__ static bool prunable(const UnitCtx &u, int64_t W, const Score &best) {
@@ -629,11 +632,13 @@ struct WaveGrp {
   __device__ int rank() const { return threadIdx.x & 63; }
   __device__ int size() const { return 64; }
   __device__ void sync() const { wave_sync(); }
+  __device__ bool any(bool x) const { return __any(x); }
 };
 struct BlockGrp {
   __device__ int rank() const { return threadIdx.x; }
   __device__ int size() const { return blockDim.x; }
   __device__ void sync() const { __syncthreads(); }
+  __device__ bool any(bool x) const { return __syncthreads_or(x); }
 };
 // A block whose accumulation table lives in global memory: its barriers must also make the
 // plain stores and atomics of every wave visible to the others.
@@ -892,7 +897,8 @@ __device__ inline uint32_t lm_unit_coop(Grp grp, Tab tab, const V &g, const Solv
   if (sd.rest) {
     double kmax = (double)c.k;
     for (int o = 1; o < c.mp; o <<= 1) kmax = fmax(kmax, __shfl_xor(kmax, o, 64));
-    if (r == 0) settle(sd, u, out, P::slack(u, stay, best, hW > 0 ? hW : 0), kmax);
+    const bool tied = LeavesTies<P>::value && grp.any(u.tied);
+    if (r == 0) settle(sd, u, out, P::slack(u, stay, best), kmax, tied);
   }
   grp.sync();
   return out;
@@ -971,8 +977,10 @@ __device__ inline uint32_t lm_unit(Grp grp, Tab tab, const V &g, const SolveDev 
   uint32_t out = kNone;
   if (P::cmp(g, u, sd, sig, best, stay) > 0)
     out = best.lab == kNone ? fresh_of(sd, fresh_base) + (uint32_t)g.orig(v) : best.lab;
-  if (r == 0 && sd.rest)
-    settle(sd, u, out, P::slack(u, stay, best, hW > 0 ? hW : 0), profile_max(g, u));
+  if (sd.rest) {
+    const bool tied = LeavesTies<P>::value && grp.any(u.tied);
+    if (r == 0) settle(sd, u, out, P::slack(u, stay, best), profile_max(g, u), tied);
+  }
   grp.sync();
   return out;
 }
@@ -1121,17 +1129,14 @@ __device__ inline void lm_group_block(const V &g, const SolveDev &sd, const int3
     typename P::Score s = P::make(g, u, sd, sig, c, wsum, kTarget);
     if (better<P>(g, u, sd, sig, s, best)) best = s;
   }
-  int64_t Wmax = cand ? wsum : 0;   // largest weight to a candidate
+  const uint64_t gmask = (G == 64 ? ~0ull : ((1ull << G) - 1)) << gbase;
   for (int m = G / 2; m >= 1; m >>= 1) {
     typename P::Score o = P::shfl(best, m);
     if (better<P>(g, u, sd, sig, o, best)) best = o;
-    if (IsMulti<P>::value && sd.rest) {
-      const int64_t w2 = shfl_xor64(Wmax, m);
-      Wmax = w2 > Wmax ? w2 : Wmax;
-    }
   }
+  const bool tied = LeavesTies<P>::value && (__ballot(u.tied) & gmask) != 0;
   if (pc.c) {
-    unsigned long long nc = __popcll(__ballot(cand) & (((G == 64) ? ~0ull : ((1ull << G) - 1)) << gbase));
+    unsigned long long nc = __popcll(__ballot(cand) & gmask);
     if (gl == 0) {
       atomicAdd(pc.c + 0, 1ull);
       atomicAdd(pc.c + 1, (unsigned long long)(row.hi - row.lo));
@@ -1146,7 +1151,7 @@ __device__ inline void lm_group_block(const V &g, const SolveDev &sd, const int3
     if (P::cmp(g, u, sd, sig, best, stay) > 0)
       out = best.lab == kNone ? fresh_of(sd, fresh_base) + (uint32_t)g.orig(v) : best.lab;
     em.put(pos + idx, out);
-    if (sd.rest) settle(sd, u, out, P::slack(u, stay, best, Wmax), profile_max(g, u));
+    if (sd.rest) settle(sd, u, out, P::slack(u, stay, best), profile_max(g, u), tied || u.tied);
   }
 }
 
@@ -1386,7 +1391,7 @@ __device__ inline void lm0_lockstep(const ViewP &g, const SolveDev &sd, int64_t 
         uc.gs0 = gs[u];
         uc.k0 = k0;
         uc.pb = pb;
-        settle(sd, uc, out, (double)(stay - best.g), 0.0);
+        settle(sd, uc, out, (double)(stay - best.g), 0.0, false);
       }
     }
     (void)p;
@@ -1957,7 +1962,10 @@ __global__ __launch_bounds__(64) void k_hub_final(V g, SolveDev sd, WinLevel L, 
       if (P::cmp(g, u, sd, sig, best, stay) > 0)
         out = best.lab == kNone ? fresh_of(sd, fresh_base) + (uint32_t)g.orig(v) : best.lab;
       Emit{target, L.first_move + r, it.colour}.put(it.pos, out);
-      if (sd.rest) settle(sd, u, out, P::slack(u, stay, best, -1), profile_max(g, u));
+      // the near-ties of the blocks that scanned the table are not known here
+      const bool tied = LeavesTies<P>::value && u.m > 1;
+      if (sd.rest)
+        settle(sd, u, out, P::slack(u, stay, best), tied ? 0.0 : profile_max(g, u), tied);
     }
   }
 }
