@@ -65,17 +65,22 @@ constexpr int32_t kRedoUnset = 0x7f7f7f7f;   // four equal bytes: set by a byte 
 // `slack` between staying and the best target the unit goes on staying while
 // 2 p b k dM <= slack, dM the degree moved in its slice since (or, spanning several slices,
 // 2 p b max_s(k_s) sum_s dM_s / S_s <= slack); targets that were pruned by q*W alone stay below the
-// best of that time.  `limit` is the counter value up to which that holds, rounded down; a
-// neighbour's move sets it to -1.  Skipping such units changes no decision.
+// best of that time.  That holds while the counter is below `limit`; a neighbour's move sets it to
+// 0.  Skipping such units changes no decision.
+//
+// A counter stays below 2^64: a sweep moves a unit at most once, so per sweep a slice's counter
+// grows by at most its total (below 2^31) and a solve's by at most 2^32 per snapshot, or per copy
+// under the CPM (S = 1), and 1 per profile entry for rounding up; snapshots, copies and entries are
+// each no more than the units of level 0, and those times the sweeps stay below 2^32.
 struct Rest {
-  int64_t limit;
+  uint64_t limit;
   int32_t ctr;    // the counter: the unit's Sigma slice, or nsl + solve
   int32_t pad;
 };
 __device__ inline bool at_rest(const SolveDev &sd, int64_t v) {
   if (!sd.rest) return false;
   const Rest r = sd.rest[v];
-  return sd.ctr[r.ctr] <= r.limit;
+  return (uint64_t)sd.ctr[r.ctr] < r.limit;
 }
 
 __device__ inline uint32_t fresh_of(const SolveDev &sd, uint32_t fresh_base) {
@@ -273,16 +278,18 @@ __device__ inline UnitCtx unit_ctx(const V &g, const SolveDev &sd, int64_t v, ui
 __device__ inline void settle(const SolveDev &sd, const UnitCtx &u, uint32_t out, double slack,
                               double kmax, bool tied) {
   if (!sd.rest) return;
-  Rest r{-1, 0, 0};
+  Rest r{0, 0, 0};
   if (out == kNone && slack >= 0.0 && !tied) {
     const bool one = u.m <= 1;
     r.ctr = one ? (u.m ? u.gs0 : 0) : sd.nsl + u.j;
     const double den = 2.0 * (double)u.pb * (one ? (double)u.k0 : kmax);
     if (den == 0.0) {
-      r.limit = INT64_MAX;
+      r.limit = ~0ull;
     } else {
       const double room = slack / den * (one ? 1.0 : 0x1p32) * (1.0 - 0x1p-30);
-      r.limit = sd.ctr[r.ctr] + (int64_t)(room < 0x1p61 ? room : 0x1p61);
+      const uint64_t now = (uint64_t)sd.ctr[r.ctr], left = ~0ull - now - 1;
+      const uint64_t more = (uint64_t)(room < 0x1p61 ? room : 0x1p61);
+      r.limit = now + 1 + (more < left ? more : left);
     }
   }
   sd.rest[u.v] = r;
@@ -1991,7 +1998,7 @@ __device__ inline void apply_sigma(const V &g, const SolveDev &sd, const SliceTa
 // entry e of a moved unit: its neighbour is not at rest any more, and reads the new label C
 template <class V>
 __device__ inline void apply_entry(const V &g, const SolveDev &sd, int64_t e, uint32_t C) {
-  if (sd.rest) sd.rest[g.col[e] & 0x7fffffff].limit = -1;
+  if (sd.rest) sd.rest[g.col[e] & 0x7fffffff].limit = 0;
   if constexpr (std::is_same<V, ViewP>::value) {
     if (g.elab) g.elab[g.prev[e]] = C;
   }

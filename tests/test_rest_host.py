@@ -131,3 +131,11 @@ def test_no_rest_without_a_settled_decision(ask):
     free = [(m, pb, k, 5, s, 0, 0, [5, 10 ** 17]) for m in (0, 1, 2) for pb, k in ((0, 3), (2, 0))
             for s in (0.0, 1.0)]
     assert all(all(got) for got in ask(free))
+
+
+@pytest.mark.parametrize("ctr", [2 ** 63 - 2 ** 40, 2 ** 63 - 1, 2 ** 63, 2 ** 64 - 2 ** 41])
+def test_counters_beyond_63_bits_end_rest(ask, ctr):
+    """The moved degree of a CPM solve adds up to 2^64 when every copy moves in every sweep."""
+    case = (2, 3, 10, ctr, 60.0 * 0.5, 0, 0)          # rests for half a unit of moved degree
+    got, = ask([case + ([ctr, ctr + 2 ** 30, ctr + 2 ** 31 + 1, ctr + 2 ** 40],)])
+    assert got == [True, True, False, False]
