@@ -7,8 +7,8 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <exception>
 #include <string>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -107,8 +107,8 @@ mslm_status check_desc_edges(const mslm_graph_desc *d) {
   for (int k = 1; k < parts; k++) {
     try {
       helpers[k] = std::thread(part, k);
-    } catch (const std::system_error &) {
-      part(k);   // no more threads to be had
+    } catch (const std::exception &) {
+      part(k);   // no thread to be had, or no memory for one
     }
   }
   part(0);
