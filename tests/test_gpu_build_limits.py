@@ -49,7 +49,7 @@ def test_totals_beyond_the_bound_are_refused(weights, on_device):
 
 
 @pytest.mark.parametrize("on_device", [False, True], ids=["host", "device"])
-@pytest.mark.parametrize("count", [1, 2, 4095, 4096, 4097, 9001])
+@pytest.mark.parametrize("count", [1, 2, 255, 32767, 32768, 32769, 70001])
 def test_totals_below_the_bound_are_built(count, on_device):
     """As many copies of an edge as one block totals, one fewer and one more."""
     from paper_2608_03695_amd import mslm
