@@ -283,6 +283,23 @@ struct Coef {
   const int64_t *S;        // [slices] device
 };
 
+// ------------------------------------------------------------------ slice denominators
+// A slice's denominator S in the estimates.  d == 0: of(a) = a * r with r = L/S, an integer (the
+// solve's slices have a common denominator L that a double holds).  Else of(a) = a / d rounded
+// once, from r = 1/d: q = a * r is off by less than two units in its last place, the remainder
+// a - q * d, a multiple of that unit below 2^33 of it, comes out of the fma exactly, and q plus
+// remainder * r is a/d but for 2^-52 units, while for d < 2^31 no quotient lies within 2^-32 units
+// of the middle between two doubles (Markstein, IBM J. Res. Dev. 34(1), 1990).  A product with
+// the rounded 1/d alone is off by up to two units: its bound holds as well, but near-ties grow.
+struct SliceRecip {
+  double r, d;
+  __host__ __device__ double of(double a) const {
+    const double q = a * r;
+    return d == 0.0 ? q : fma(fma(-q, d, a), r, q);
+  }
+};
+// end of the slice denominators
+
 // ------------------------------------------------------------------ exact comparison
 // Fixed-width two's-complement integers of kLimbs 32-bit limbs (2304 bits): enough for
 // q*W*prod(S) with 64 slice denominators below 2^31 plus the summed null terms.

@@ -32,10 +32,11 @@ struct SolveDev {
   const int32_t *sfirst;               // first global slice of the solve
   const int64_t *S;                    // per global slice: 2m_s, or 1 for an empty slice
   // doubles of the multi-slice estimates: values are scaled by L, the least common multiple of the
-  // solve's S when it is below 2^53 (else 1).  rS: per global slice L/S (an integer then);
-  // scale: per solve L, then from index J on the bound below which a scaled value is exact (2^53,
-  // or 0 when L is not used)
-  const double *rS, *scale;
+  // solve's S when it is below 2^53 (else 1).  rS: per global slice a -> a * L / S; scale: per solve
+  // L, then from index J on the bound below which a scaled value is exact (2^53, or 0 when L is not
+  // used)
+  const SliceRecip *rS;
+  const double *scale;
   int J;
   int64_t *fallbacks;                  // exact-comparison counter per solve
   // per solve: the smallest mark of a near-tie that a kernel without the big-integer path could
@@ -454,7 +455,7 @@ struct PolicyKT {
         int64_t k;
         g.pent(u.v, jj, gs, k);
         int64_t y = target_y(tab, gs, k, lab, kind);
-        double t = (double)(k * y) * sd.rS[gs];
+        double t = sd.rS[gs].of((double)(k * y));
         acc += t;
         mag += fabs(t);
       }
@@ -745,7 +746,7 @@ struct CoopLane {
   int j;           // this lane's slice index within the profile (valid when j < m)
   bool valid;
   int64_t k;       // unit degree in that slice
-  double r;        // that slice's scaled 1/S
+  SliceRecip r;    // that slice's denominator
   const uint64_t *sub;
   uint32_t mask;
   int shift;
@@ -759,7 +760,7 @@ __device__ inline CoopLane coop_lane(const V &g, const UnitCtx &u, const SolveDe
   c.j = rank & (c.mp - 1);
   c.valid = c.j < u.m;
   c.k = 0;
-  c.r = 0.0;
+  c.r = SliceRecip{0.0, 0.0};
   c.sub = tab.slots;
   c.mask = 0;
   c.shift = 32;
@@ -816,7 +817,7 @@ __device__ inline ScoreK coop_score(const UnitCtx &u, const CoopLane &c, uint32_
   double t = 0.0;
   if (c.valid && kind != kEmpty) {
     if (kind == kStay) y -= c.k;
-    t = (double)(c.k * y) * c.r;
+    t = c.r.of((double)(c.k * y));
   }
   double acc = t, mag = fabs(t);
   for (int o = 1; o < c.mp; o <<= 1) {
@@ -2967,7 +2968,7 @@ __global__ __launch_bounds__(256) void k_ref_wc(V g, SolveDev sd, const int32_t 
       c0 = c;
     }
     m++;
-    double t = (double)c * sd.rS[gs];
+    double t = sd.rS[gs].of((double)c);
     acc += t;
     mag += fabs(t);
   }
