@@ -2664,7 +2664,9 @@ constexpr int kJpDepth = 16;       // links of a chain followed in one round
 constexpr int kJpSlots = 2048;     // units a block may queue in one round
 constexpr int kJpChainRow = 2048;  // longer rows take the block
 constexpr int kJpChainWords = (kJpChainRow + 64) / 64;
-constexpr int kJpUnitBits = 27;    // unit ids stay below 2^32 / 33 < 2^27: the depth sits above
+constexpr int kJpUnitBits = 27;    // the depth sits above the unit id: chains are followed only in
+                                   // levels of at most 2^27 units (graphs hold fewer than 2^32 / 33
+                                   // and unions at most 100 * 2^20, whatever a solve's sweeps)
 static_assert(kJpDepth <= 1 << (31 - kJpUnitBits), "unit and depth fit 31 bits: -1 is an empty slot");
 constexpr uint32_t kJpPolls = 1u << 22;   // ends a wave's wait (seconds) should its block stall
 
@@ -2686,7 +2688,10 @@ struct JpQueue {
         const uint32_t h = load(head), t = load(tail);
         if (h < (t < kJpSlots ? t : kJpSlots)) {
           if (atomicCAS(head, h, h + 1) != h) continue;
-          while ((got = (int32_t)load((uint32_t *)slot + h)) < 0) {}   // claimed: its owner fills it
+          // whoever claimed it in push() fills it next and waits for nobody; bounded all the same
+          for (uint32_t k = 0; k < kJpPolls; k++)
+            if ((got = (int32_t)load((uint32_t *)slot + h)) >= 0) break;
+          if (got < 0) atomicOr(failed, 1u);
           break;
         }
         if (listed) {
