@@ -113,6 +113,7 @@ struct Workspace {
   Buf ref_snap_a, ref_snap_p;             // active flags and proposal stamps before a round
   Buf ref_keep;                           // active flags of solves that skip a round's redo
   Buf win_tab, win_segs, win_items, win_state;   // colour windows of the level being swept
+  Buf win_work;                           // work of each colour (counting solves)
   Buf rest_ctr;                           // degree moved per Sigma slice and per solve
   // sweeps replayed from HIP graphs: a private stream (default priority) joined to the solve
   // stream by events, the fresh-label base on the device, and a switch that turns graphs off

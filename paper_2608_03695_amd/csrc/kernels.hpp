@@ -845,10 +845,18 @@ constexpr int kCoopBatch = 4;
 // One unit: accumulate neighbour-community weights in the table, evaluate every candidate
 // community (strictly better gain wins, ties to the lower label, the empty community has
 // gain 0 and label +inf), and decide a move only when it beats staying strictly.
-// Profiling counters of the decision kernels (filled only when profiling is requested):
-// [0] units decided, [1] entries scanned, [2] candidate communities evaluated.
+// Counters of the decision kernels (filled only when counting is requested), kLmWords per colour of
+// the level: [0] units decided, [1] entries scanned, [2] candidate communities evaluated in the
+// present window, from 4 on the most of each in the sweep's earlier windows.  When a colour's
+// decisions count, k_win_apply adds the most that one window decided of it to the level's total:
+// what was decided ahead in vain is not the schedule's work, and a unit that was decided ahead and
+// is still at rest when its colour's turn comes is.
+constexpr int kLmWords = 8;
 struct LmCounters {
   unsigned long long *c;
+  __device__ LmCounters of(int colour) const {
+    return LmCounters{c ? c + kLmWords * colour : nullptr};
+  }
 };
 
 template <class P, class Grp, class Tab, class V>
@@ -1600,8 +1608,8 @@ __global__ __launch_bounds__(256, kWinWaves<P>) void k_win_multi(V g, SolveDev s
     const WinItem it = L.items[i];
     const Emit em{target, L.first_move + r, it.colour};
     sd.mark = it.colour;
-    win_item<P, kSmallBlockLg>(g, sd, units, it, comm, sig, em, fresh_base, pc, sk, sv, sl, sn, red,
-                               hw, hl);
+    win_item<P, kSmallBlockLg>(g, sd, units, it, comm, sig, em, fresh_base, pc.of(it.colour), sk, sv,
+                               sl, sn, red, hw, hl);
     __syncthreads();   // the next item lays its tables over this one's
   }
 }
@@ -1636,10 +1644,11 @@ __global__ __launch_bounds__(256) void k_win_all(V g, SolveDev sd, WinLevel L, i
     const Emit em{target, L.first_move + r, it.colour};
     sd.mark = it.colour;
     if (!std::is_same<P, P1>::value && it.slot >= kNumBins)
-      win_item<P1, LG>(g, sd, units, it, comm, sig, em, fresh_base, pc, sk, sv, sl, sn, red1, hw,
-                       hl);
+      win_item<P1, LG>(g, sd, units, it, comm, sig, em, fresh_base, pc.of(it.colour), sk, sv, sl, sn,
+                       red1, hw, hl);
     else
-      win_item<P, LG>(g, sd, units, it, comm, sig, em, fresh_base, pc, sk, sv, sl, sn, red, hw, hl);
+      win_item<P, LG>(g, sd, units, it, comm, sig, em, fresh_base, pc.of(it.colour), sk, sv, sl, sn,
+                      red, hw, hl);
     __syncthreads();   // the next item lays its tables over this one's
   }
 }
@@ -1663,20 +1672,20 @@ __global__ __launch_bounds__(256, IsMulti<P>::value ? 1 : 8) void k_win_groups(V
     sd.mark = it.colour;
     switch (it.slot % kNumBins) {
       case 0:
-        lm_group_block<P, V, 4>(g, sd, units, it.pos, it.count, comm, sig, em, fresh_base, pc, lk,
-                                lv);
+        lm_group_block<P, V, 4>(g, sd, units, it.pos, it.count, comm, sig, em, fresh_base,
+                                 pc.of(it.colour), lk, lv);
         break;
       case 1:
-        lm_group_block<P, V, 8>(g, sd, units, it.pos, it.count, comm, sig, em, fresh_base, pc, lk,
-                                lv);
+        lm_group_block<P, V, 8>(g, sd, units, it.pos, it.count, comm, sig, em, fresh_base,
+                                 pc.of(it.colour), lk, lv);
         break;
       case 2:
-        lm_group_block<P, V, 16>(g, sd, units, it.pos, it.count, comm, sig, em, fresh_base, pc, lk,
-                                 lv);
+        lm_group_block<P, V, 16>(g, sd, units, it.pos, it.count, comm, sig, em, fresh_base,
+                                 pc.of(it.colour), lk, lv);
         break;
       default:
-        lm_group_block<P, V, 32>(g, sd, units, it.pos, it.count, comm, sig, em, fresh_base, pc, lk,
-                                 lv);
+        lm_group_block<P, V, 32>(g, sd, units, it.pos, it.count, comm, sig, em, fresh_base,
+                                 pc.of(it.colour), lk, lv);
     }
   }
 }
@@ -1698,20 +1707,20 @@ __global__ __launch_bounds__(256, 8) void k_win_lm0(ViewP g, SolveDev sd, WinLev
     const Emit em{target, L.first_move + r, it.colour};
     switch (it.slot) {
       case 0:
-        lm0_lockstep<4, U, kOne, kCopy>(g, sd, it.pos, it.count, comm, sig, em, fresh_base, pc,
-                                        keys, vals);
+        lm0_lockstep<4, U, kOne, kCopy>(g, sd, it.pos, it.count, comm, sig, em, fresh_base,
+                                        pc.of(it.colour), keys, vals);
         break;
       case 1:
-        lm0_lockstep<8, U, kOne, kCopy>(g, sd, it.pos, it.count, comm, sig, em, fresh_base, pc,
-                                        keys, vals);
+        lm0_lockstep<8, U, kOne, kCopy>(g, sd, it.pos, it.count, comm, sig, em, fresh_base,
+                                        pc.of(it.colour), keys, vals);
         break;
       case 2:
-        lm0_lockstep<16, U, kOne, kCopy>(g, sd, it.pos, it.count, comm, sig, em, fresh_base, pc,
-                                         keys, vals);
+        lm0_lockstep<16, U, kOne, kCopy>(g, sd, it.pos, it.count, comm, sig, em, fresh_base,
+                                        pc.of(it.colour), keys, vals);
         break;
       default:
-        lm0_lockstep<32, U, kOne, kCopy>(g, sd, it.pos, it.count, comm, sig, em, fresh_base, pc,
-                                         keys, vals);
+        lm0_lockstep<32, U, kOne, kCopy>(g, sd, it.pos, it.count, comm, sig, em, fresh_base,
+                                        pc.of(it.colour), keys, vals);
     }
   }
 }
@@ -1742,7 +1751,7 @@ __global__ __launch_bounds__(NT) void k_win_block(V g, SolveDev sd, WinLevel L, 
     const WinItem it = L.items[i];
     sd.mark = it.colour;
     const uint32_t out = lm_unit<P>(BlockGrp(), tab, g, sd, g.unit_at(units, it.pos), comm, sig,
-                                    fresh_base, red, pc, hw, hl);
+                                    fresh_base, red, pc.of(it.colour), hw, hl);
     if (threadIdx.x == 0) Emit{target, L.first_move + r, it.colour}.put(it.pos, out);
     __syncthreads();
   }
@@ -1834,8 +1843,9 @@ __global__ __launch_bounds__(256) void k_hub_accum(V g, SolveDev sd, WinLevel L,
     for (int i = threadIdx.x; i < (1 << kHubLdsLg); i += blockDim.x)
       if (sk[i] != 0) tab.add(sk[i] - 1, sv[i]);
     if (pc.c && blockIdx.x == 0 && threadIdx.x == 0) {
-      atomicAdd(pc.c + 0, 1ull);
-      atomicAdd(pc.c + 1, (unsigned long long)(row.hi - row.lo));
+      unsigned long long *c = pc.of(L.items[win.i0 + y].colour).c;
+      atomicAdd(c + 0, 1ull);
+      atomicAdd(c + 1, (unsigned long long)(row.hi - row.lo));
     }
     __syncthreads();   // the tables are reused for the next hub
   }
@@ -1923,7 +1933,7 @@ __global__ __launch_bounds__(256) void k_hub_eval(V g, SolveDev sd, WinLevel L, 
         if (better<P>(g, u, sd, sig, sc, best)) best = sc;
       }
     }
-    if (pc.c && ncand) atomicAdd(pc.c + 2, (unsigned long long)ncand);
+    if (pc.c && ncand) atomicAdd(pc.of(it.colour).c + 2, (unsigned long long)ncand);
     best = group_best<P>(BlockGrp(), g, u, sd, sig, best, red);
     if (threadIdx.x == 0) part[(int64_t)(win.i0 + y - hub0) * gridDim.x + blockIdx.x] = best;
   }
@@ -2009,7 +2019,8 @@ template <class V>
 __global__ __launch_bounds__(256) void k_win_apply(V g, SolveDev sd, WinLevel L, int r,
                                                    const int32_t *units, const uint32_t *target,
                                                    uint32_t *comm, SliceTable sig,
-                                                   uint32_t *moved) {
+                                                   uint32_t *moved, LmCounters pc,
+                                                   unsigned long long *total) {
   __shared__ uint32_t s_moves;
   const WinState s = L.st[r];
   const int f = L.first_move[r];
@@ -2033,6 +2044,15 @@ __global__ __launch_bounds__(256) void k_win_apply(V g, SolveDev sd, WinLevel L,
         L.first_move[(r + 2) % 3] = kNoColour;
       }
     }
+    if (pc.c && live)
+      for (int i = 4 * s.c0 + threadIdx.x; i < 4 * s.c1; i += blockDim.x) {
+        unsigned long long *now = pc.of(i / 4).c + i % 4, *most = now + 4;
+        const unsigned long long m = *now > *most ? *now : *most;
+        const bool counts = i / 4 <= f;
+        if (counts && m) atomicAdd(total + i % 4, m);
+        *now = 0;
+        *most = counts ? 0 : m;
+      }
     if (L.near_tie)
       for (int j = threadIdx.x; j < L.J; j += blockDim.x) {
         const int c = L.near_tie[r * L.J + j];
