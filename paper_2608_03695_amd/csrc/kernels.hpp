@@ -635,15 +635,26 @@ struct GTab {
   __device__ void reset(int) const {}
 };
 
+// The thread's index for one work item.  Kernels that loop over items take it anew for each: the
+// compiler would keep what follows from it, lane positions and LDS addresses of every bin's code, in
+// registers across the loop.  That cost the window kernels 64 registers and 15 spilled (k_win_lm0,
+// now 52), 124 (k_win_multi at level 0, now 71) and 211 (k_win_all of aggregated levels, now 157);
+// the 32 level-0 sweeps of 64M units took 1225 ms with it, 1030 without.
+__device__ inline int item_thread() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
 // Group = the threads cooperating on one unit: one wave, or a whole block.
 struct WaveGrp {
-  __device__ int rank() const { return threadIdx.x & 63; }
+  __device__ int rank() const { return item_thread() & 63; }
   __device__ int size() const { return 64; }
   __device__ void sync() const { wave_sync(); }
   __device__ bool any(bool x) const { return __any(x); }
 };
 struct BlockGrp {
-  __device__ int rank() const { return threadIdx.x; }
+  __device__ int rank() const { return item_thread(); }
   __device__ int size() const { return blockDim.x; }
   __device__ void sync() const { __syncthreads(); }
   __device__ bool any(bool x) const { return __syncthreads_or(x); }
@@ -1070,10 +1081,10 @@ __device__ inline void lm_group_block(const V &g, const SolveDev &sd, const int3
                                       int64_t pos, int count, const uint32_t *comm,
                                       const SliceTable &sig, const Emit &em, uint32_t fresh_base,
                                       LmCounters pc, uint32_t *lk, int64_t *lv) {
-  const int lane = threadIdx.x & 63;
+  const int tid = item_thread(), lane = tid & 63;
   const int gl = lane & (G - 1);
   const int gbase = lane & ~(G - 1);
-  const int idx = threadIdx.x / G;
+  const int idx = tid / G;
   if (idx >= count) return;   // whole groups leave together; shuffles stay inside a group
   const int64_t v = g.unit_at(units, pos + idx);
   if ((sd.frozen && sd.frozen[g.solve_of(v)]) || at_rest(sd, v)) {   // nothing to decide
@@ -1098,9 +1109,9 @@ __device__ inline void lm_group_block(const V &g, const SolveDev &sd, const int3
   bool leader = false;
   {
     constexpr int kSlots = 2 * G;
-    uint32_t *sk = lk + (threadIdx.x >> 6) * 128 + (gbase / G) * kSlots;
+    uint32_t *sk = lk + (tid >> 6) * 128 + (gbase / G) * kSlots;
     unsigned long long *sv =
-        reinterpret_cast<unsigned long long *>(lv) + (threadIdx.x >> 6) * 128 + (gbase / G) * kSlots;
+        reinterpret_cast<unsigned long long *>(lv) + (tid >> 6) * 128 + (gbase / G) * kSlots;
     sk[gl] = 0u;
     sk[gl + G] = 0u;
     sv[gl] = 0ull;
@@ -1213,10 +1224,10 @@ __device__ inline void lm0_lockstep(const ViewP &g, const SolveDev &sd, int64_t 
                                     const Emit &em, uint32_t fresh_base, LmCounters pc,
                                     uint32_t *lm0_keys, unsigned long long *lm0_vals) {
   constexpr int kGroups = 256 / G;
-  const int lane = threadIdx.x & 63;
+  const int tid = item_thread(), lane = tid & 63;
   const int gl = lane & (G - 1);
   const int gbase = lane & ~(G - 1);
-  const int base = threadIdx.x / G;
+  const int base = tid / G;
   if (base >= count) return;   // whole groups leave together
   int64_t pos[U];
   bool live[U];
@@ -1278,8 +1289,8 @@ __device__ inline void lm0_lockstep(const ViewP &g, const SolveDev &sd, int64_t 
   // adds its raw weight (low half) or coupling multiplier (high half) to its label's slot; the
   // lane that claims a slot leads that label.  Three LDS steps instead of G shuffle rounds.
   constexpr int kSlots = 2 * G;   // load at most one half
-  uint32_t *sk = lm0_keys + (threadIdx.x >> 6) * (U * 128) + (gbase / G) * kSlots;
-  unsigned long long *sv = lm0_vals + (threadIdx.x >> 6) * (U * 128) + (gbase / G) * kSlots;
+  uint32_t *sk = lm0_keys + (tid >> 6) * (U * 128) + (gbase / G) * kSlots;
+  unsigned long long *sv = lm0_vals + (tid >> 6) * (U * 128) + (gbase / G) * kSlots;
 #pragma unroll
   for (int u = 0; u < U; u++) {
     sk[u * 128 + gl] = 0u;
@@ -1553,7 +1564,7 @@ __device__ inline void win_item(const V &g, const SolveDev &sd, const int32_t *u
                                sv);
       break;
     case 4: {
-      const int wv = threadIdx.x >> 6;
+      const int tid = item_thread(), wv = tid >> 6;
       if (wv >= it.count) break;
       // a unit of at most 64 entries in fewer than kCoopMinM slices: the wave as one lane group
       // (entries one per lane, labels merged in this wave's LDS region)
@@ -1569,7 +1580,7 @@ __device__ inline void win_item(const V &g, const SolveDev &sd, const int32_t *u
                  sn + wv};
       const uint32_t out = lm_unit<P>(WaveGrp(), tab, g, sd, v, comm, sig, fresh_base,
                                       (typename P::Score *)nullptr, pc);
-      if ((threadIdx.x & 63) == 0) em.put(it.pos + wv, out);
+      if ((tid & 63) == 0) em.put(it.pos + wv, out);
       break;
     }
     default: {
@@ -1581,9 +1592,8 @@ __device__ inline void win_item(const V &g, const SolveDev &sd, const int32_t *u
   }
 }
 
-// Waves per SIMD that the registers are held to (the exact policy needs scratch anyway): 4 instead
-// of the compiler's 3 took the level-0 kernel of a 3.2M-unit solve from 39.1 to 36.5 ms, 8 instead
-// of 5 the lane-group kernels from 34 to 30 ms; 5 lost to spills.
+// Waves per SIMD that the registers must allow (the exact policy needs scratch anyway); see
+// item_thread for what they come to.
 template <class P>
 constexpr int kWinWaves = std::is_same<P, PolicyK>::value ? 1 : IsMulti<P>::value ? 3 : 4;
 
