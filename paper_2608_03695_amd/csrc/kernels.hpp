@@ -1498,16 +1498,23 @@ struct WinRange {
 // Window from colour c0 on (one wave): as many colours as the budget holds, at least one, up to
 // and including the next colour that moved in the last sweep (it will probably move again, and
 // what lies behind it would be decided twice); below `floor` blocks the chip is not full and
-// deciding further ahead costs nothing.
+// deciding further ahead costs nothing, except for hubs, whose kernels take their time by
+// themselves: no colour with a hub is decided behind one that will probably move (one hub of 8000
+// entries in the last of 14 colours was decided five times a sweep).
 __device__ inline int win_end(const WinLevel &L, int t, int c0, int budget) {
   const int lane = threadIdx.x & 63;
   const int lim = budget > L.floor ? budget : L.floor;
+  const int32_t *hubs = L.ip + kFamHub * (L.ncol + 1);
   int c1 = c0;
   const int base = c0 < L.ncol ? L.cost[c0] : 0;
+  bool moves = false;   // a colour before c1 will probably move
   while (c1 < L.ncol) {
     const int c = c1 + lane;
     const int cost = c < L.ncol ? L.cost[c + 1] - base : 0;
-    const bool in = c < L.ncol && (c == c0 || cost <= lim);
+    const uint64_t likely = __ballot(c < L.ncol && (t == 0 || L.moved_at[c] >= t - 1));
+    const bool behind = moves || (likely & ((1ull << lane) - 1));
+    moves = moves || likely;
+    const bool in = c < L.ncol && (c == c0 || (cost <= lim && !(behind && hubs[c + 1] > hubs[c])));
     const bool stop = in && cost > L.floor && L.moved_at[c] >= t - 1;
     const uint64_t out = ~__ballot(in), stops = __ballot(stop);
     const int n_in = out ? __builtin_ctzll(out) : 64;
