@@ -107,7 +107,7 @@ typedef struct {
                                      MSLM_PROFILE: time every level-0 local-moving decision
                                      launch with HIP events on the graph's stream (the short
                                      launches of aggregated levels are left untimed);
-                                     MSLM_COUNT: count the work of those kernels            */
+                                     MSLM_COUNT: count the work of the decisions            */
   uint32_t reserved1;
   const int64_t *gamma_slices;
   const int32_t *initial_membership;
@@ -134,8 +134,10 @@ typedef struct {
   double lm_kernel_ms;            /* summed durations of the timed decision launches
                                      (MSLM_PROFILE: level 0 only, equal to lm0_kernel_ms)     */
   int64_t lm_launches;            /* number of those launches (MSLM_PROFILE)                 */
-  int64_t lm_units, lm_entries, lm_candidates;   /* work of those kernels: units decided,
-                                     adjacency entries scanned, candidate communities (COUNT) */
+  int64_t lm_units, lm_entries, lm_candidates;   /* work of the decisions that take effect: units
+                                     decided, adjacency entries scanned, candidate communities
+                                     (COUNT; decisions made ahead in vain are not in it, nor are
+                                     units that a sweep leaves at rest)                       */
   int64_t q_components[3 * 64 + 1];
   double lm0_kernel_ms;           /* level-0 decision kernel time (MSLM_PROFILE)              */
   int64_t lm0_launches;           /* level-0 decision launches (MSLM_PROFILE)                 */
@@ -202,7 +204,8 @@ mslm_status mslm_q_exact_variant(const int64_t *q_components, int32_t n_slices, 
  *   copy_moves         level 0: the per-entry neighbour-label copy is kept through sweeps that
  *                      moved at most (units / copy_moves) units (1..2^30, default 1024)
  *   lat_parts_max      a sweep decides at least this many times 32 blocks of work ahead of the
- *                      colour whose moves come next (1..16, default 16)
+ *                      colour whose moves come next, where no hub unit (above 4096 entries) comes
+ *                      before (1..16, default 16)
  *   batch_units        mslm_batch_leiden: most supra-nodes per union, in units of 2^20 (1..100,
  *                      default 24)
  * Errors: EINVAL for a value out of range or a NULL pointer. */
@@ -260,7 +263,7 @@ mslm_status mslm_set_allocator(void *(*alloc)(size_t bytes, void *ctx),
  * the last call's contents; every call clears what it needs.  Calls on one GPU share its
  * array: the library runs them one at a time (a per-device lock), and a call's device work is
  * finished when it returns, so calls from several threads never overlap on the array.
- * Errors: EUNSUPPORTED when the solve needs more than the array holds (estimate: 96 bytes per
+ * Errors: EUNSUPPORTED when the solve needs more than the array holds (estimate: 104 bytes per
  * CSR entry plus 384 per supra-node plus 1 MiB: about 400k supra-nodes with 1M entries), EINVAL for
  * MSLM_PROFILE (it records HIP events) or when the current device is not the graph's, and as
  * mslm_leiden otherwise. */

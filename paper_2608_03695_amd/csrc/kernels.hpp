@@ -1631,11 +1631,12 @@ __global__ __launch_bounds__(256, kWinWaves<P>) void k_win_multi(V g, SolveDev s
   }
 }
 
-// Every bin below the hubs of a window of small colours, in one launch: such windows are bound by
-// latency, and one launch over both classes (units of class 1, slots from kNumBins on, by P1, the
-// others by P) takes the place of up to five in a row.  LG: the rows fill at most half the table;
-// small tables let more blocks share a CU.  Blocks of 512 threads cost the exact policy's levels a
-// quarter (57k units: 67.5 ms against 53.7) and gained a tenth or less elsewhere.
+// Every bin below the hubs of a window of small colours (but for the block bin where make_windows
+// keeps that apart), in one launch: such windows are bound by latency, and one launch over both
+// classes (units of class 1, slots from kNumBins on, by P1, the others by P) takes the place of up to
+// five in a row.  LG: the rows fill at most half the table; small tables let more blocks share a CU.
+// Blocks of 512 threads cost the exact policy's levels a quarter (57k units: 67.5 ms against 53.7)
+// and gained a tenth or less elsewhere.
 template <class P, class P1, class V, int LG>
 __global__ __launch_bounds__(256) void k_win_all(V g, SolveDev sd, WinLevel L, int r,
                                                          const int32_t *units,
