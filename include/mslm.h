@@ -204,8 +204,8 @@ mslm_status mslm_q_exact_variant(const int64_t *q_components, int32_t n_slices, 
  *   copy_moves         level 0: the per-entry neighbour-label copy is kept through sweeps that
  *                      moved at most (units / copy_moves) units (1..2^30, default 1024)
  *   lat_parts_max      a sweep decides at least this many times 32 blocks of work ahead of the
- *                      colour whose moves come next, where no hub unit (above 4096 entries) comes
- *                      before (1..16, default 16)
+ *                      colour whose moves come next (level 0: or up to a hub unit, one of more than
+ *                      4096 entries; 1..16, default 16)
  *   batch_units        mslm_batch_leiden: most supra-nodes per union, in units of 2^20 (1..100,
  *                      default 24)
  * Errors: EINVAL for a value out of range or a NULL pointer. */

@@ -1463,6 +1463,7 @@ struct WinLevel {
   int32_t *first_move;  // [3] smallest moving colour of the pair's window
   int32_t *near_tie;    // [3][J] smallest colour of each solve with an unsettled near-tie
   int32_t ncol, floor, J;
+  int32_t hubs_last;    // no colour with a hub is decided behind one that will probably move
 };
 constexpr int32_t kNoColour = 0x7fffffff;
 constexpr int kXcds = 8;   // MI355X: eight accelerator complex dies, each with its own L2
@@ -1499,8 +1500,10 @@ struct WinRange {
 // and including the next colour that moved in the last sweep (it will probably move again, and
 // what lies behind it would be decided twice); below `floor` blocks the chip is not full and
 // deciding further ahead costs nothing, except for hubs, whose kernels take their time by
-// themselves: no colour with a hub is decided behind one that will probably move (one hub of 8000
-// entries in the last of 14 colours was decided five times a sweep).
+// themselves: one hub of 8000 entries in the last of 14 colours was decided five times a sweep.
+// At level 0 (hubs_last) such colours wait until nothing before them will probably move; aggregated
+// levels have hubs in many colours, and the windows that this adds cost as much as it saves (a solve
+// of 250k units 62.8 -> 64.5 ms).
 __device__ inline int win_end(const WinLevel &L, int t, int c0, int budget) {
   const int lane = threadIdx.x & 63;
   const int lim = budget > L.floor ? budget : L.floor;
@@ -1514,7 +1517,8 @@ __device__ inline int win_end(const WinLevel &L, int t, int c0, int budget) {
     const uint64_t likely = __ballot(c < L.ncol && (t == 0 || L.moved_at[c] >= t - 1));
     const bool behind = moves || (likely & ((1ull << lane) - 1));
     moves = moves || likely;
-    const bool in = c < L.ncol && (c == c0 || (cost <= lim && !(behind && hubs[c + 1] > hubs[c])));
+    const bool wait = L.hubs_last && behind && c < L.ncol && hubs[c + 1] > hubs[c];
+    const bool in = c < L.ncol && (c == c0 || (cost <= lim && !wait));
     const bool stop = in && cost > L.floor && L.moved_at[c] >= t - 1;
     const uint64_t out = ~__ballot(in), stops = __ballot(stop);
     const int n_in = out ? __builtin_ctzll(out) : 64;
